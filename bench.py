@@ -65,8 +65,8 @@ HBM_PEAK_GBS = 8000.0
 # that lay out the data they read (a profile's counters stand only while these hash to the
 # value recorded with them)
 KERNEL_SOURCES = [os.path.join(ROOT, "paper_2605_30728_amd", "csrc", f)
-                  for f in ("ibp_kernels.hip", "ibp_cache_kernels.hip", "ibp_wave.hpp", "ibp_device.hpp",
-                            "ibp_runtime.hip", "ibp_meta_slots.cpp")]
+                  for f in ("ibp_kernels.hip", "ibp_gather_kernels.hip", "ibp_cache_kernels.hip", "ibp_wave.hpp",
+                            "ibp_device.hpp", "ibp_runtime.hip", "ibp_meta_slots.cpp")]
 
 
 def code_sha256(texts):
@@ -121,8 +121,7 @@ def kernel_name(workload, W, part=False):
             return f"k_part_batched<{k},{maxr},{ {1: 8, 2: 4, 4: 2, 8: 1}[k] },{src}>"
         return f"k_part_rows<{k},{maxr},{src}>"
     if workload in GATHERS:
-        rb = {1: 8, 2: 4, 4: 2, 8: 1}[k]
-        return f"k_gather_rows<{k},{rb}>" if W <= 512 else "k_gather_tiled"
+        return f"k_gather_slots<{min(k, 4)}>"   # every workload's clusters have metadata slots
     return f"k_decompress<{k},{ {1: 4, 2: 4, 4: 2, 8: 1}[k] },true>"   # device payload: split window loads
 
 

@@ -119,11 +119,12 @@ typedef struct {
     uint64_t host_pack_ns;   /* host time spent gathering packed rows into staging */
     uint64_t gather_meta_bytes; /* device metadata a row gather reads per cluster it
                                 touches: a compact slot when the stream uses the clustered
-                                scheme, rows of at most 2048 bytes and every cluster
-                                repeats at most 16 distinct (Mask, Bitval) pairs over its
-                                words (128 bytes at up to 512-byte rows and 8 pairs), else
-                                the 2 * row_bytes of Mask and Bitval. A property of the
-                                handle: ibp_reset_stats leaves it */
+                                scheme and every cluster repeats at most 16 distinct (Mask,
+                                Bitval) pairs over its words (128 bytes at up to 512-byte
+                                rows and 8 pairs; with the payload in place in host memory
+                                only for rows of at most 2048 bytes), else the
+                                2 * row_bytes of Mask and Bitval. A property of the handle:
+                                ibp_reset_stats leaves it */
 } ibp_stats;
 
 /* Open flags: where the packed payload lives after ibp_open. */
@@ -210,8 +211,9 @@ ibp_status ibp_describe(const void *stream, uint64_t stream_bytes, ibp_desc *d);
  * memory for the whole dataset), and the payload goes to device memory or stays in
  * library-owned pinned host memory to be read over PCIe on demand (Sec. 5, PCIe transfer
  * compression; Sec. 4.4), see the flags. Derived device copies are added where they
- * serve the gathers: compact per-cluster metadata slots (clustered streams, rows of at
- * most 2 KiB) and the per-row offsets packed 60 rows to a 128-byte line (thresholded
+ * serve the gathers: compact per-cluster metadata slots (clustered streams; rows of at
+ * most 2 KiB for the zero-copy placements), with those 16 bytes per cluster (where its
+ * rows are) and a table of row tiles, and the per-row offsets packed 60 rows to a 128-byte line (thresholded
  * streams, rows of at most 1,092 bytes); ibp_memory_usage reports the total. The payload
  * copies the kernels read in place (device, zero-copy) of a clustered stream whose rows
  * are mostly whole 128-byte lines start every cluster on a line (at most 127 bytes of

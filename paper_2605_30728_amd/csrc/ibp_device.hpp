@@ -8,6 +8,13 @@
 namespace ibp {
 namespace dev {
 
+// A cluster's rows in the payload that the kernels read (clustered scheme).
+struct GroupInfo {
+    uint64_t off;      // byte of its first row
+    uint32_t stride;   // bytes from one row to the next
+    uint32_t bits;     // packed bits of a row
+};
+
 // What the kernels need to know about a stream resident on the device.
 struct DevStream {
     const uint32_t *meta;    // per group: Mask[W] then Bitval[W] (32-bit words)
@@ -30,6 +37,12 @@ struct DevStream {
     const uint8_t *slots;
     uint32_t slot_pairs;
     uint32_t slot_bytes;
+    const GroupInfo *groups; // non-null: the slots' indices are in word order, and the
+                             // gathers are launch_gather_slots's
+    // with those, rows of more than 256 words: per cluster, the packed bit at which every
+    // 128-word tile of a row starts, tiles128 = ceil(W / 128) entries
+    const uint32_t *tile_bits;
+    uint32_t tiles128;
     // participation scheme, rows of at most 65535 / kRowLineRows bytes: the row offsets
     // line-packed, one 128-byte line per kRowLineRows rows (see row_span); null: the
     // kernels read `index`
@@ -69,6 +82,16 @@ hipError_t launch_decompress(const DevStream &s, const uint8_t *payload, uint64_
 hipError_t launch_gather(const DevStream &s, const uint8_t *payload, const int64_t *ids,
                          const uint32_t *sg, const uint32_t *soff, uint64_t n, void *out,
                          unsigned long long *err, hipStream_t stream);
+
+// The same gather for streams with word-order slots and the payload (or the stage) in device
+// memory (ibp_gather_kernels.hip); launch_gather sends those here.
+hipError_t launch_gather_slots(const DevStream &s, const uint8_t *payload, const int64_t *ids, const uint32_t *sg,
+                               const uint32_t *soff, uint64_t n, void *out, unsigned long long *err,
+                               hipStream_t stream);
+
+// Fills groups[0..n_groups) (from s.meta, s.index and s.row_align) and, unless null, the
+// tile_bits table (n_groups * s.tiles128 entries) of a clustered-scheme stream.
+hipError_t launch_group_info(const DevStream &s, GroupInfo *groups, uint32_t *tile_bits, hipStream_t stream);
 
 // Hit / miss counters of a cache: kCountLines pairs, one per 128-byte line.
 inline constexpr uint32_t kCountLines = 64;

@@ -94,11 +94,20 @@ private:
 // Compact device metadata of the clustered scheme's row gathers (ibp_meta_slots.cpp): a
 // fixed-size slot per cluster, cluster g at g * slot bytes, with its distinct (Mask, Bitval)
 // pairs (room for 8, or for 16 when some cluster has more than 8) and a 4-bit pair index per
-// word, laid out for lanes owning K words each. Returns the pairs per slot (8 or 16), or 0
-// when some cluster has more than 16 distinct pairs (no slots).
+// word: in lane order, for lanes owning the K words l, l + 64, ... (rows of at most 512
+// words), or, with word_order, word w's index in bits [4w, 4w + 4) (rows of any size).
+// Returns the pairs per slot (8 or 16), or 0 when some cluster has more than 16 distinct
+// pairs (no slots).
 constexpr uint64_t meta_slot_bytes(uint32_t pairs, uint32_t K) { return (8ull * pairs + 32ull * K + 127) / 128 * 128; }
+// The same for rows of W words; wider rows than 512 words have an index area of whole
+// 256-word tiles.
+constexpr uint64_t meta_slot_bytes_of(uint32_t pairs, uint32_t W) {
+    return W <= 64    ? meta_slot_bytes(pairs, 1)
+           : W <= 128 ? meta_slot_bytes(pairs, 2)
+                      : meta_slot_bytes(pairs, 4 * ((W + 255) / 256));
+}
 uint32_t build_meta_slots(const uint8_t *meta, uint64_t n_groups, uint32_t W, uint32_t K, Pool &pool,
-                          std::vector<uint8_t> &slots);
+                          std::vector<uint8_t> &slots, bool word_order = false);
 
 // Line-packed row offsets of a participation-scheme stream (ibp_meta_slots.cpp), from its
 // per-row index off[0..n_rows] (unaligned u64s at index_bytes): one 128-byte line per R

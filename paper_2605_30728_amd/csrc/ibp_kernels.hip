@@ -739,11 +739,6 @@ struct PartLoads {
     uint32_t bs[RB][K];   // bits 0-4: the window's shift; bits 5-31: all ones when the chunk is compressed
 };
 
-__device__ __forceinline__ uint64_t lane_u64(uint64_t v, uint32_t i) {
-    return ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(v >> 32), (int)i) << 32) |
-           (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)v, (int)i);
-}
-
 // m ? a : b, bit by bit, in one instruction (written out, the compiler splits it into a
 // not, an and and an and-or, and keeps every row's inverted mask live)
 __device__ __forceinline__ uint32_t bit_select(uint32_t m, uint32_t a, uint32_t b) {
@@ -1254,6 +1249,7 @@ hipError_t launch_gather(const DevStream &s, const uint8_t *payload, const int64
                          const uint32_t *soff, uint64_t n, void *out, unsigned long long *err, hipStream_t stream) {
     if (n == 0) return hipSuccess;
     if (s.part_m) return launch_part(s, payload, 0, ids, sg, soff, 0, n, out, err, stream);
+    if (s.slots && s.groups) return launch_gather_slots(s, payload, ids, sg, soff, n, out, err, stream);
     const auto *p = reinterpret_cast<const uint32_t *>(payload);
     auto *o = static_cast<uint32_t *>(out);
     const int k = words_per_lane(s.W);
@@ -1284,9 +1280,8 @@ hipError_t launch_gather(const DevStream &s, const uint8_t *payload, const int64
     dim3 grid((unsigned)blocks), block(kBlock);
     auto go = [&](auto kk, auto rb) {
         constexpr int KK = decltype(kk)::value, R = decltype(rb)::value;
-        if (soff) {
-            if (s.slots) hipLaunchKernelGGL((k_gather_rows<KK, R, true, kMetaSlots>), grid, block, 0, stream, s, p, ids, sg, soff, n, o, seg, err);
-            else hipLaunchKernelGGL((k_gather_rows<KK, R, true, kMetaRaw>), grid, block, 0, stream, s, p, ids, sg, soff, n, o, seg, err);
+        if (soff) {   // (a stage is device memory: with slots the gather above took it)
+            hipLaunchKernelGGL((k_gather_rows<KK, R, true, kMetaRaw>), grid, block, 0, stream, s, p, ids, sg, soff, n, o, seg, err);
         } else {
             if (s.slots) hipLaunchKernelGGL((k_gather_rows<KK, R, false, kMetaSlots>), grid, block, 0, stream, s, p, ids, sg, soff, n, o, seg, err);
             else hipLaunchKernelGGL((k_gather_rows<KK, R, false, kMetaRaw>), grid, block, 0, stream, s, p, ids, sg, soff, n, o, seg, err);

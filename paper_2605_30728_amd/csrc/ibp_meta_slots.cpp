@@ -11,10 +11,14 @@
 //   pairs   P x {u32 Mask, u32 Bitval}: the cluster's distinct pairs in order of first
 //           appearance (unused entries zero); P = 8, or 16 when some cluster of the
 //           stream has more than 8
-//   index   32*K bytes: a 4-bit pair index per word, laid out for the wave that decodes
-//           the row: lane l owns words l, l+64, ..., l+64*(K-1) and their K indices sit
-//           together in bits [4*K*l, 4*K*l + 4*K) of the area (index j in bits 4j..4j+3
-//           of that field), so a lane fetches all of its indices with one load
+//   index   a 4-bit pair index per word, so that a lane fetches all of its indices with
+//           one load. Word order (payload or stage in device memory: a lane owns K
+//           consecutive words): word w's index in bits [4w, 4w + 4). Lane order (payload
+//           read in place from host memory): lane l owns words l, l+64, ..., l+64*(K-1)
+//           and their K indices sit together in bits [4*K*l, 4*K*l + 4*K) of the area
+//           (index j in bits 4j..4j+3 of that field). 32*K bytes, K the words per lane of
+//           rows of at most 512 words; whole 256-word tiles of 128 bytes beyond (word
+//           order only)
 //
 // padded to whole 128-byte lines. Words past the row's end (lanes of the last tile) take
 // index 0. A slot's address follows from the cluster number alone, so its loads need
@@ -72,7 +76,7 @@ uint32_t cluster_pairs(const uint8_t *mg, uint32_t W, uint32_t *pm, uint32_t *pb
 }  // namespace
 
 uint32_t build_meta_slots(const uint8_t *meta, uint64_t n_groups, uint32_t W, uint32_t K, Pool &pool,
-                          std::vector<uint8_t> &slots) {
+                          std::vector<uint8_t> &slots, bool word_order) {
     const uint64_t raw = 8ull * W;
     // pass 1: the most distinct pairs of any cluster
     std::atomic<uint32_t> most{0};
@@ -89,8 +93,8 @@ uint32_t build_meta_slots(const uint8_t *meta, uint64_t n_groups, uint32_t W, ui
         slots.clear();
         return 0;
     }
-    const uint64_t S = meta_slot_bytes(P, K);
-    slots.assign(std::max<uint64_t>(n_groups * S, 8), 0);
+    const uint64_t S = word_order ? meta_slot_bytes_of(P, W) : meta_slot_bytes(P, K);
+    slots.assign(std::max<uint64_t>(n_groups, 1) * S, 0);
     // pass 2: the slots
     pool.run(n_groups, 1024, [&](uint64_t lo, uint64_t hi) {
         std::vector<uint8_t> word_pair(W);
@@ -103,6 +107,10 @@ uint32_t build_meta_slots(const uint8_t *meta, uint64_t n_groups, uint32_t W, ui
                 std::memcpy(slot + 8ull * k + 4, &pb[k], 4);
             }
             uint8_t *idx = slot + 8ull * P;
+            if (word_order) {
+                for (uint32_t w = 0; w < W; ++w) idx[w >> 1] |= (uint8_t)(word_pair[w] << (4 * (w & 1)));
+                continue;
+            }
             for (uint32_t l = 0; l < 64; ++l)
                 for (uint32_t j = 0; j < K; ++j) {
                     const uint32_t w = l + 64 * j;

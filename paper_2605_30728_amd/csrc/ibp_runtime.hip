@@ -196,6 +196,8 @@ struct ibp_handle {
     dev::DevStream ds{};
     uint32_t *d_meta = nullptr;
     uint8_t *d_slots = nullptr;           // compact metadata of the row gathers (clustered, W <= 512)
+    dev::GroupInfo *d_groups = nullptr;   // with word-order slots: per cluster, where its rows are
+    uint32_t *d_tile_bits = nullptr;      // with word-order slots, W > 256: first bits of the row tiles
     uint8_t *d_row_lines = nullptr;       // line-packed row offsets (participation, rows <= 1092 B)
     uint64_t *d_index = nullptr;
     uint8_t *d_payload = nullptr;
@@ -302,12 +304,16 @@ ibp_status check_handle(ibp_handle *h, const CallScope &cs) {
 void release_handle(ibp_handle *h) {
     dev_free(h->d_meta);
     dev_free(h->d_slots);
+    dev_free(h->d_groups);
+    dev_free(h->d_tile_bits);
     dev_free(h->d_row_lines);
     dev_free(h->d_index);
     dev_free(h->d_payload);
     dev_free(h->d_err);
     h->d_meta = nullptr;
     h->d_slots = nullptr;
+    h->d_groups = nullptr;
+    h->d_tile_bits = nullptr;
     h->d_row_lines = nullptr;
     h->d_index = nullptr;
     h->d_payload = nullptr;
@@ -735,20 +741,30 @@ ibp_status open_impl(const void *stream, uint64_t stream_bytes, int device, uint
         hipMemset(h->d_err, 0, 8) != hipSuccess)
         return bail(fail(IBP_EHIP, "index upload failed"));
     const uint32_t W = d.row_bytes / 4;
-    if (d.flags == 0 && W <= 512) {
+    // gathers from device memory (payload or stage) read word-order slots, of rows of any
+    // size; those that read host memory in place lane-order ones
+    const bool word_order = flags == IBP_OPEN_PAYLOAD_DEVICE || flags == IBP_OPEN_PAYLOAD_HOST;
+    if (d.flags == 0 && (W <= 512 || word_order)) {
         // the row gathers read a cluster's metadata for every row they decode: when every
         // cluster fits one, give each a compact slot as well
         const uint32_t K = (uint32_t)dev::words_per_lane(W);
         check_alloc();
         std::vector<uint8_t> slots;
-        const uint32_t P = build_meta_slots(v.meta(), d.n_groups, W, K, *h->pool, slots);
+        const uint32_t P = build_meta_slots(v.meta(), d.n_groups, W, K, *h->pool, slots, word_order);
         if (P) {
             if (dev_alloc(&h->d_slots, slots.size()) != hipSuccess)
                 return bail(fail(IBP_ENOMEM, "device allocation for metadata failed"));
             if (hipMemcpy(h->d_slots, slots.data(), slots.size(), hipMemcpyHostToDevice) != hipSuccess)
                 return bail(fail(IBP_EHIP, "metadata upload failed"));
             h->ds.slot_pairs = P;
-            h->ds.slot_bytes = (uint32_t)meta_slot_bytes(P, K);
+            h->ds.slot_bytes = (uint32_t)(word_order ? meta_slot_bytes_of(P, W) : meta_slot_bytes(P, K));
+            if (word_order) {
+                h->ds.tiles128 = (W + 127) / 128;
+                if (dev_alloc(&h->d_groups, std::max<uint64_t>(d.n_groups, 1) * sizeof(dev::GroupInfo)) != hipSuccess ||
+                    (W > 256 && dev_alloc(&h->d_tile_bits, std::max<uint64_t>(d.n_groups, 1) * 4 * h->ds.tiles128) !=
+                                    hipSuccess))
+                    return bail(fail(IBP_ENOMEM, "device allocation for metadata failed"));
+            }
         }
     }
     if ((d.flags & IBP_STREAM_PARTICIPATION) && d.n_rows > 0 && d.n_rows <= ~0ull / dev::kRowLineRows &&
@@ -799,9 +815,10 @@ ibp_status open_impl(const void *stream, uint64_t stream_bytes, int device, uint
     for (int j = 0; j < kIdSlots; ++j)
         if (hipEventCreateWithFlags(&h->ev_ids_free[j], hipEventDisableTiming) != hipSuccess)
             return bail(fail(IBP_EHIP, "event creation failed"));
-    if (hipDeviceSynchronize() != hipSuccess) return bail(fail(IBP_EHIP, "upload did not complete"));
     h->ds.meta = h->d_meta;
     h->ds.slots = h->d_slots;
+    h->ds.groups = h->d_groups;
+    h->ds.tile_bits = h->d_tile_bits;
     h->ds.row_lines = h->d_row_lines;
     h->ds.rl_magic = dev::div_magic(dev::kRowLineRows);
     h->ds.index = h->d_index;
@@ -813,6 +830,9 @@ ibp_status open_impl(const void *stream, uint64_t stream_bytes, int device, uint
     h->ds.payload_host = flags == IBP_OPEN_PAYLOAD_HOST_ZERO_COPY || flags == IBP_OPEN_PAYLOAD_HOST_ZERO_COPY_ALIGNED;
     h->ds.W = d.row_bytes / 4;
     h->ds.G = d.group_rows;
+    if (h->d_groups && dev::launch_group_info(h->ds, h->d_groups, h->d_tile_bits, nullptr) != hipSuccess)
+        return bail(fail(IBP_EHIP, "metadata kernel failed"));
+    if (hipDeviceSynchronize() != hipSuccess) return bail(fail(IBP_EHIP, "upload did not complete"));
     ignore(hipSetDevice(prev));
     prev = -1;
     *out = h;

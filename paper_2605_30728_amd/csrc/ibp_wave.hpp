@@ -128,6 +128,38 @@ __device__ __forceinline__ uint32_t row_dword(__amdgpu_buffer_rsrc_t r, uint32_t
     return (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(r, (int)(q * 4u), 0, 0);
 }
 
+// A per-lane 64-bit value, read from one lane.
+__device__ __forceinline__ uint64_t lane_u64(uint64_t v, uint32_t i) {
+    return ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(v >> 32), (int)i) << 32) |
+           (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)v, (int)i);
+}
+// The same of a device memory address (global, so that its loads are not flat ones).
+typedef const __attribute__((address_space(1))) uint8_t *GlobalBytes;
+__device__ __forceinline__ GlobalBytes lane_ptr(const uint8_t *p, uint32_t i) {
+    return (GlobalBytes)lane_u64(reinterpret_cast<uint64_t>(p), i);
+}
+
+// Orders a wave's own LDS writes before its later reads by other lanes (a wave's LDS
+// accesses are performed in order: no instruction is needed, only the compiler's order).
+__device__ __forceinline__ void wave_lds_fence() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// The D dwords of a row from the one that holds bit `bit`. SPLIT: as D loads (the dwords'
+// offsets in the scalar operand keep the compiler from merging them; the range check
+// subtracts that operand from the range, which must be at least 4 * (D - 1)), else as one.
+template <int D, bool SPLIT>
+__device__ __forceinline__ void row_window(__amdgpu_buffer_rsrc_t r, uint32_t bit, uint32_t (&d)[D]) {
+    const uint32_t at = (bit >> 5) * 4u;
+#pragma unroll
+    for (int k = 0; k < D; ++k) {
+        if constexpr (SPLIT) d[k] = (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(r, (int)at, 4 * k, 0);
+        else d[k] = (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(r, (int)(at + 4u * k), 0, 0);
+    }
+}
+
 // A word's 64-bit window as two dword loads (dwords q and q + 1 of p). The compiler would
 // merge them into one 8-byte load, which is misaligned for every odd q; an opaque second
 // index keeps them two 4-byte loads. Measured: the 111M-row gather 830 -> 695 us, the bf16

@@ -1,0 +1,111 @@
+"""GPU parity of the gathers that read word-order metadata slots (payload or stage in device
+memory), at the sizes where their tiling can go wrong: one, two and four words per lane and
+rows of several 256-word tiles, one word to either side of each boundary; slots of 8 and 16
+pairs (8 and 4 items per wave); words of one, two, three, four and more runs of variant bits,
+mixed within one wave; batches that end inside a wave; ids outside the table. Expected rows
+are the rows themselves (the scheme is lossless), compressed by the CPU oracle; exact."""
+import sys
+
+import numpy as np
+import pytest
+
+import oracle
+import paper_2605_30728_amd as ibp
+
+pytestmark = pytest.mark.gpu
+
+# masks of the invariant bits of a word, by the runs of variant bits they leave
+RUNS = {0: 0xFFFFFFFF, 1: 0xFF80007F, 2: 0x7F00FFFF, 3: 0x0F0FF0FF, 4: 0xF00FF00F, 5: 0x33333FFF, 16: 0x55555555,
+        32: 0x00000000}
+
+
+@pytest.fixture(scope="module")
+def torch():
+    import torch as t
+    assert t.cuda.is_available()
+    ibp.lib()
+    return t
+
+
+def rows_of_runs(W, n, G, kinds, seed):
+    """n rows of W words; cluster c's words cycle through the masks of kinds[c % len(kinds)]."""
+    rng = np.random.default_rng(seed)
+    out = np.empty((n, W), np.uint32)
+    for c in range((n + G - 1) // G):
+        r0, r1 = c * G, min(n, c * G + G)
+        masks = np.array([RUNS[k] for k in kinds[c % len(kinds)]], np.uint32)[np.arange(W) % len(kinds[c % len(kinds)])]
+        value = rng.integers(0, 1 << 32, size=len(masks), dtype=np.uint64).astype(np.uint32)
+        value = value[np.arange(W) % len(kinds[c % len(kinds)])]    # few distinct (Mask, Bitval) pairs
+        noise = rng.integers(0, 1 << 32, size=(r1 - r0, W), dtype=np.uint64).astype(np.uint32)
+        if r1 - r0 < G:
+            noise[:] = 0                       # few rows would agree on random bits
+        out[r0:r1] = (value & masks) | (noise & ~masks)
+    return out.view(np.uint8).reshape(n, 4 * W)
+
+
+KINDS = {"two": [(1,), (2, 0, 1), (0,)],                      # up to two runs, and rows of no bits
+         "four": [(1, 2), (3, 1), (4, 2, 0), (2,)],           # three and four in some items
+         "any": [(1,), (5, 2), (16, 32, 3), (32,)]}           # the holes deposit in some items
+
+
+@pytest.mark.parametrize("placement", ["device_ids", "host_ids", "staged"])
+@pytest.mark.parametrize("kind", sorted(KINDS))
+@pytest.mark.parametrize("W", [1, 2, 63, 64, 65, 127, 128, 129, 255, 256, 257, 511, 513, 768, 769, 1025])
+def test_word_order_slots(torch, W, kind, placement):
+    G = 40                                     # noise bits then vary in every cluster
+    n = G * len(KINDS[kind]) * 2 + 3           # a ragged last cluster
+    L = 4 * W
+    rows = rows_of_runs(W, n, G, KINDS[kind], seed=W)
+    stream = oracle.compress(rows, G)
+    rng = np.random.default_rng(W)
+    flags = ibp.IBP_OPEN_PAYLOAD_HOST if placement == "staged" else ibp.IBP_OPEN_PAYLOAD_DEVICE
+    print(f"[gather tiles] W={W} {kind} {placement}", file=sys.stderr, flush=True)
+    with ibp.ibp_open(stream, 0, flags) as h:
+        k = 1 if W <= 64 else 2 if W <= 128 else 4 * ((W + 255) // 256)
+        assert ibp.ibp_get_stats(h)["gather_meta_bytes"] == (8 * 8 + 32 * k + 127) // 128 * 128
+        for count in (1, 5, 8, 9, 3 * n):      # inside a wave, a whole one, one past it
+            ids = rng.integers(0, n, size=count).astype(np.int64)
+            ids[-1] = n - 1
+            out = torch.full((count * L + 64,), 0xA5, dtype=torch.uint8, device="cuda")
+            if placement == "device_ids":
+                bad = rng.random(count) < 0.1
+                sent = np.where(bad, np.where(rng.random(count) < 0.5, -1 - ids, n + ids), ids)
+                ibp.ibp_gather_decompress_device(h, torch.from_numpy(sent).cuda(), out, out_cap=count * L)
+            else:
+                bad = np.zeros(count, bool)
+                ibp.ibp_gather_decompress(h, ids, out, out_cap=count * L)
+            torch.cuda.synchronize()
+            got = out[:count * L].cpu().numpy().reshape(count, L)
+            want = rows[ids].copy()
+            want[bad] = 0
+            assert np.array_equal(got, want), (count, np.flatnonzero((got != want).any(1))[:8])
+            assert (out[count * L:].cpu().numpy() == 0xA5).all(), "wrote past the output"
+            assert ibp.ibp_device_errors(h) == bad.sum()
+
+
+@pytest.mark.parametrize("W", [48, 100, 200, 600])
+def test_sixteen_pairs(torch, W):
+    """Slots of 16 pairs: four items per wave, and a cluster of exactly 16."""
+    G, n = 32, 32 * 9 + 1
+    rng = np.random.default_rng(W)
+    masks = np.array([RUNS[k] for k in (1, 2, 3, 4)], np.uint32)
+    rows = np.empty((n, W), np.uint32)
+    for c in range(0, n, G):
+        p = 1 + (c // G * 7) % 16 if c else 16
+        m = masks[np.arange(p) % 4]
+        v = np.arange(p, dtype=np.uint32) * np.uint32(0x11111111)
+        m = m | np.uint32(0xF) if p > 4 else m
+        pat = np.arange(W) % p
+        noise = rng.integers(0, 1 << 32, size=(min(G, n - c), W), dtype=np.uint64).astype(np.uint32)
+        rows[c:c + G] = (v & m)[pat] | (noise & ~m[pat])
+    rows[-1] = 0
+    L = 4 * W
+    rows = rows.view(np.uint8).reshape(n, L)
+    ids = rng.integers(0, n, size=2001).astype(np.int64)
+    with ibp.ibp_open(oracle.compress(rows, G), 0) as h:
+        k = 1 if W <= 64 else 2 if W <= 128 else 4 * ((W + 255) // 256)
+        assert ibp.ibp_get_stats(h)["gather_meta_bytes"] == (8 * 16 + 32 * k + 127) // 128 * 128
+        out = torch.empty(ids.size * L, dtype=torch.uint8, device="cuda")
+        ibp.ibp_gather_decompress_device(h, torch.from_numpy(ids).cuda(), out)
+        torch.cuda.synchronize()
+        assert np.array_equal(out.cpu().numpy().reshape(-1, L), rows[ids])
