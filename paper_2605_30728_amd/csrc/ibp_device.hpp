@@ -37,10 +37,12 @@ struct DevStream {
     const uint8_t *slots;
     uint32_t slot_pairs;
     uint32_t slot_bytes;
-    const GroupInfo *groups; // non-null: the slots' indices are in word order, and the
-                             // gathers are launch_gather_slots's
-    // with those, rows of more than 256 words: per cluster, the packed bit at which every
-    // 128-word tile of a row starts, tiles128 = ceil(W / 128) entries
+    uint32_t word_order;     // 1: the slots' indices are in word order, and the gathers are
+                             // launch_gather_slots's
+    // clustered scheme, payload or stage in device memory, and slots or rows of more than
+    // 128 words: where each cluster's rows are, and for those wider rows the packed bit at
+    // which every 128-word tile of a row starts, tiles128 = ceil(W / 128) entries per cluster
+    const GroupInfo *groups;
     const uint32_t *tile_bits;
     uint32_t tiles128;
     // participation scheme, rows of at most 65535 / kRowLineRows bytes: the row offsets

@@ -48,22 +48,6 @@ struct PairDeposit {
     uint32_t nm, bv, p0, p1;
 };
 
-// N neighbouring words in one store, non-temporal (see store_out).
-template <int N>
-__device__ __forceinline__ void store_words(__amdgpu_buffer_rsrc_t r, uint32_t byte, const uint32_t (&v)[N]) {
-    constexpr int kNonTemporal = 2;   // the instruction's cache policy bits
-    if constexpr (N == 1) {
-        __builtin_amdgcn_raw_buffer_store_b32(v[0], r, (int)byte, 0, kNonTemporal);
-    } else {
-        typedef uint32_t vec __attribute__((ext_vector_type(N)));
-        vec x;
-#pragma unroll
-        for (int k = 0; k < N; ++k) x[k] = v[k];
-        if constexpr (N == 2) __builtin_amdgcn_raw_buffer_store_b64(x, r, (int)byte, 0, kNonTemporal);
-        else __builtin_amdgcn_raw_buffer_store_b128(x, r, (int)byte, 0, kNonTemporal);
-    }
-}
-
 __device__ __forceinline__ uint32_t bfi(uint32_t m, uint32_t a, uint32_t b) { return (a & m) | (b & ~m); }
 
 __device__ __forceinline__ uint32_t first_bit(uint32_t v) { return (uint32_t)__builtin_ctz(v | 0x80000000u); }

@@ -127,18 +127,24 @@ __device__ __forceinline__ uint32_t word_generic(uint32_t bv, uint32_t nm, uint3
     return acc;
 }
 
-// Decode RB rows of one cluster. `at.byte(i)` is the payload byte where row i's packed
-// bits start and `at.out(i)` the row's output; both are wave-uniform. All loads of the
-// batch are issued before any word is rebuilt, so RB*K loads are in flight per wave.
-// NR >= 0 applies NR precomputed runs per word; NR < 0 takes the generic loop.
-template <int NR, int RB, int K, int MAXR, class At>
+// Decode rows 0 .. min(RB, n) - 1 of one cluster (n >= RB unless PART). `at.byte(i)` is the
+// payload byte where row i's packed bits start and `at.out(i)` the row's output; both are
+// wave-uniform. All loads of the batch are issued before any word is rebuilt, so RB*K loads
+// are in flight per wave. NR >= 0 applies NR precomputed runs per word; NR < 0 takes the
+// generic loop. A row is stored through a buffer descriptor of its own, whose range check
+// drops the lanes past the row's end and, with an empty range, the rows past n (which repeat
+// the last row's loads), without branches; non-temporally: with three output buffers in turn
+// 42.0 us against 46.7 with plain stores (bf16 KV layer, 134 MB out, 16-row batches), with
+// one buffer that every call writes again, whose lines plain stores find in the last-level
+// cache, 41.6 against 40.3 (exec-masked plain stores before: 48.9 and 42.1; now 40.0 and 40.5).
+template <int NR, int RB, bool PART, int K, int MAXR, class At>
 __device__ __forceinline__ void decode_batch(const Tile<K, MAXR> &t, const uint32_t *__restrict__ pay32,
-                                             const At &at, uint32_t W, uint32_t w0) {
+                                             const At &at, uint32_t n, uint32_t W, uint32_t w0) {
     const uint32_t l = lane_id();
     uint32_t d0[RB][K], d1[RB][K], b[RB][K];
 #pragma unroll
     for (int i = 0; i < RB; ++i) {
-        const uint64_t rbyte = at.byte(i);
+        const uint64_t rbyte = at.byte(PART ? min((uint32_t)i, n - 1) : (uint32_t)i);
         const uint32_t *__restrict__ p = pay32 + (rbyte >> 2);
         const uint32_t bit0 = ((uint32_t)rbyte & 3u) * 8u;
 #pragma unroll
@@ -154,27 +160,32 @@ __device__ __forceinline__ void decode_batch(const Tile<K, MAXR> &t, const uint3
     }
 #pragma unroll
     for (int i = 0; i < RB; ++i) {
-        uint32_t *__restrict__ o = at.out(i);
+        const __amdgpu_buffer_rsrc_t o = row_rsrc(at.out(i) + w0, PART && i >= (int)n ? 0u : (W - w0) * 4u);
 #pragma unroll
         for (int j = 0; j < K; ++j) {
             const uint32_t x = __builtin_amdgcn_alignbit(d1[i][j], d0[i][j], b[i][j]);
             uint32_t v;
             if constexpr (NR >= 0) v = word_fast<NR>(t, j, x);
             else v = word_generic(t.bv[j], t.nm[j], x);
-            const uint32_t w = w0 + l + kWave * j;
-            if (w < W) o[w] = v;   // plain store: streamed output, measured 7% faster than non-temporal
+            const uint32_t one[1] = {v};
+            store_words<1>(o, (l + kWave * j) * 4u, one);
         }
     }
 }
 
-// Decode rows [0, n) of one cluster with the run count fixed at compile time.
+// Decode rows [0, n) of one cluster with the run count fixed at compile time: in full
+// batches, then the rest in a partial one (K = 1) or one by one (a partial batch of a few
+// rows measured 2% slower on wide rows, whose slices are whole batches but for a cluster's
+// last one).
 template <int NR, int K, int MAXR, class At>
 __device__ __forceinline__ void decode_rows_nr(const Tile<K, MAXR> &t, const uint32_t *__restrict__ pay32,
                                                uint32_t n, const At &at, uint32_t W, uint32_t w0) {
     constexpr int RB = K <= 1 ? 8 : (K <= 2 ? 4 : (K <= 4 ? 2 : 1));
+    constexpr int TAIL = K <= 1 ? RB : 1;
     uint32_t k = 0;
-    for (; k + RB <= n; k += RB) decode_batch<NR, RB>(t, pay32, at.shifted(k), W, w0);
-    for (; k < n; ++k) decode_batch<NR, 1>(t, pay32, at.shifted(k), W, w0);
+    for (; k + RB <= n; k += RB) decode_batch<NR, RB, false>(t, pay32, at.shifted(k), RB, W, w0);
+    if constexpr (RB > 1)
+        for (; k < n; k += TAIL) decode_batch<NR, TAIL, (TAIL > 1)>(t, pay32, at.shifted(k), n - k, W, w0);
 }
 
 template <int K, int MAXR, class At>
@@ -250,13 +261,25 @@ __device__ __forceinline__ void decode_rows_tiled(const uint32_t *__restrict__ m
 }
 
 
-// One wave per unit = (cluster, slice of at most rpu rows of it).
-template <int K, int MAXR, bool SPLIT>
+// One wave per unit = (cluster, slice of at most rpu rows of it) or, TILED, (cluster, slice,
+// tile of 64K words): the cluster's tile table gives the bit at which the tile starts, so
+// the tiles of wide rows are as independent as narrow rows.
+template <int K, int MAXR, bool SPLIT, bool TILED>
 __global__ __launch_bounds__(kBlock) void k_decompress(DevStream s, const uint32_t *__restrict__ pay32,
                                                         uint64_t pay_base, uint32_t *__restrict__ out,
                                                         uint64_t first, uint64_t n, uint64_t g0,
                                                         uint64_t n_units, uint32_t upg, uint32_t rpu) {
-    const uint64_t unit = wave_slot();
+    uint64_t unit;
+    uint32_t w0 = 0;
+    if constexpr (TILED) {
+        // the tiles of a slice side by side on one XCD: neighbours share a line of every row
+        const uint64_t slot = (uint64_t)xcd_block(blockIdx.x, gridDim.x) * kWavesPerBlock +
+                              (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
+        unit = slot / s.tiles128;
+        w0 = (uint32_t)(slot - unit * s.tiles128) * (kWave * K);
+    } else {
+        unit = wave_slot();
+    }
     if (unit >= n_units) return;
     const uint64_t g = g0 + unit / upg;
     const uint64_t gstart = g * s.G;
@@ -269,7 +292,14 @@ __global__ __launch_bounds__(kBlock) void k_decompress(DevStream s, const uint32
     const uint32_t *__restrict__ mg = s.meta + g * 2ull * W;
     const uint64_t base = s.index[g] - pay_base;
     const uint32_t rows = (uint32_t)(r_hi - r_lo);
-    if (W <= (uint32_t)(kWave * K)) {
+    if constexpr (TILED) {
+        static_assert(K == 2, "the tile table is of 128-word tiles");
+        Tile<K, MAXR> t;
+        tile_setup(t, mg, W, w0, s.tile_bits[g * s.tiles128 + w0 / (kWave * K)]);
+        const uint64_t rb = s.groups[g].stride;
+        const SliceAt<SPLIT> at{base + (r_lo - gstart) * rb, rb, out + (r_lo - first) * W, W};
+        decode_rows(t, pay32, rows, at, W, w0);
+    } else if (W <= (uint32_t)(kWave * K)) {
         Tile<K, MAXR> t;
         tile_setup(t, mg, W, 0, 0);
         const uint64_t rb = row_stride((t.bits + 7u) >> 3, s.row_align);
@@ -1212,30 +1242,47 @@ hipError_t launch_decompress(const DevStream &s, const uint8_t *payload, uint64_
     if (n == 0) return hipSuccess;
     if (s.part_m) return launch_part(s, payload, pay_base, nullptr, nullptr, nullptr, first, n, out, nullptr, stream);
     const uint64_t g0 = first / s.G, g1 = (first + n - 1) / s.G;
-    // rows per wave: a whole cluster (at most 64 rows), halved while the launch would have
-    // fewer than ~16k waves (2 per wave slot of the chip), down to one batch of rows;
-    // every slice repeats its cluster's setup, which is small next to its rows
-    const int k = words_per_lane(s.W);
+    // rows per wave: a whole cluster (at most 64 rows), halved in whole batches while the
+    // launch would have fewer than 16k waves (2 per wave slot of the chip; 128k at one word
+    // per lane), down to one batch of rows; every slice repeats its cluster's setup, which is
+    // small next to its rows. Measured: 524,288 rows of 64 words 42.4 us with 32 rows per wave
+    // (16k waves), 40.5 with 8; 2,097,152 rows 160.5 and 154; 50k rows of 600 words in tiles
+    // 45.4 us at 16k waves and 47.9 at 32k
+    // Rows of more than 128 words in device memory: 128-word tiles, each a unit of its own
+    // (a wave that walks a wide row's tiles has one or two rows' loads in flight and rebuilds
+    // runs in a loop: 50k rows of 600 words of bf16 pairs 117 us, in tiles 45; 50k of 300
+    // words 38 and 17.8).
+    const bool tiled = s.tile_bits && !s.payload_host;
+    const uint32_t tiles = tiled ? s.tiles128 : 1;
+    const int k = tiled ? 2 : words_per_lane(s.W);
     const uint32_t min_rows = k == 1 ? 8 : (k == 2 ? 4 : (k == 4 ? 2 : 1));
     uint32_t rpu = s.G <= 64 ? s.G : 64;
-    while (rpu > min_rows && (g1 - g0 + 1) * ((s.G + rpu - 1) / rpu) < 16384) rpu = (rpu + 1) / 2;
+    const uint64_t enough = k == 1 ? 131072 : 16384;
+    while (rpu > min_rows && (g1 - g0 + 1) * ((s.G + rpu - 1) / rpu) * tiles < enough)
+        rpu = ((rpu + 1) / 2 + min_rows - 1) / min_rows * min_rows;
     const uint32_t upg = (s.G + rpu - 1) / rpu;
     const uint64_t n_units = (g1 - g0 + 1) * upg;
-    const uint64_t blocks = (n_units + kWavesPerBlock - 1) / kWavesPerBlock;
+    const uint64_t blocks = (n_units * tiles + kWavesPerBlock - 1) / kWavesPerBlock;
     const auto *p = reinterpret_cast<const uint32_t *>(payload);
     auto *o = static_cast<uint32_t *>(out);
     dim3 grid((unsigned)blocks), block(kBlock);
-    auto go = [&](auto kk, auto mr, auto split) {
+    auto go = [&](auto kk, auto mr, auto split, auto tile) {
         constexpr int KK = decltype(kk)::value, MR = decltype(mr)::value;
-        constexpr bool SP = decltype(split)::value;
-        hipLaunchKernelGGL((k_decompress<KK, MR, SP>), grid, block, 0, stream, s, p, pay_base, o, first, n, g0,
+        constexpr bool SP = decltype(split)::value, TI = decltype(tile)::value;
+        hipLaunchKernelGGL((k_decompress<KK, MR, SP, TI>), grid, block, 0, stream, s, p, pay_base, o, first, n, g0,
                            n_units, upg, rpu);
     };
     // two dword loads per window from device memory, one 8-byte load from pinned host memory
+    // (where a wave also takes whole rows: a tile's first and last lines would cross PCIe
+    // for each of the tiles that share them)
     auto launch = [&](auto kk, auto mr) {
-        if (s.payload_host) go(kk, mr, std::false_type{});
-        else go(kk, mr, std::true_type{});
+        if (s.payload_host) go(kk, mr, std::false_type{}, std::false_type{});
+        else if constexpr (decltype(kk)::value <= 2) go(kk, mr, std::true_type{}, std::false_type{});
     };
+    if (tiled) {
+        go(std::integral_constant<int, 2>{}, std::integral_constant<int, 4>{}, std::true_type{}, std::true_type{});
+        return hipGetLastError();
+    }
     switch (k) {
     case 1: launch(std::integral_constant<int, 1>{}, std::integral_constant<int, 4>{}); break;
     case 2: launch(std::integral_constant<int, 2>{}, std::integral_constant<int, 4>{}); break;
@@ -1249,7 +1296,7 @@ hipError_t launch_gather(const DevStream &s, const uint8_t *payload, const int64
                          const uint32_t *soff, uint64_t n, void *out, unsigned long long *err, hipStream_t stream) {
     if (n == 0) return hipSuccess;
     if (s.part_m) return launch_part(s, payload, 0, ids, sg, soff, 0, n, out, err, stream);
-    if (s.slots && s.groups) return launch_gather_slots(s, payload, ids, sg, soff, n, out, err, stream);
+    if (s.slots && s.word_order) return launch_gather_slots(s, payload, ids, sg, soff, n, out, err, stream);
     const auto *p = reinterpret_cast<const uint32_t *>(payload);
     auto *o = static_cast<uint32_t *>(out);
     const int k = words_per_lane(s.W);

@@ -196,8 +196,8 @@ struct ibp_handle {
     dev::DevStream ds{};
     uint32_t *d_meta = nullptr;
     uint8_t *d_slots = nullptr;           // compact metadata of the row gathers (clustered, W <= 512)
-    dev::GroupInfo *d_groups = nullptr;   // with word-order slots: per cluster, where its rows are
-    uint32_t *d_tile_bits = nullptr;      // with word-order slots, W > 256: first bits of the row tiles
+    dev::GroupInfo *d_groups = nullptr;   // DevStream::groups
+    uint32_t *d_tile_bits = nullptr;      // DevStream::tile_bits
     uint8_t *d_row_lines = nullptr;       // line-packed row offsets (participation, rows <= 1092 B)
     uint64_t *d_index = nullptr;
     uint8_t *d_payload = nullptr;
@@ -758,14 +758,15 @@ ibp_status open_impl(const void *stream, uint64_t stream_bytes, int device, uint
                 return bail(fail(IBP_EHIP, "metadata upload failed"));
             h->ds.slot_pairs = P;
             h->ds.slot_bytes = (uint32_t)(word_order ? meta_slot_bytes_of(P, W) : meta_slot_bytes(P, K));
-            if (word_order) {
-                h->ds.tiles128 = (W + 127) / 128;
-                if (dev_alloc(&h->d_groups, std::max<uint64_t>(d.n_groups, 1) * sizeof(dev::GroupInfo)) != hipSuccess ||
-                    (W > 256 && dev_alloc(&h->d_tile_bits, std::max<uint64_t>(d.n_groups, 1) * 4 * h->ds.tiles128) !=
-                                    hipSuccess))
-                    return bail(fail(IBP_ENOMEM, "device allocation for metadata failed"));
-            }
+            h->ds.word_order = word_order;
         }
+    }
+    if (d.flags == 0 && word_order && (h->d_slots || W > 128)) {
+        h->ds.tiles128 = (W + 127) / 128;
+        const uint64_t ng = std::max<uint64_t>(d.n_groups, 1);
+        if (dev_alloc(&h->d_groups, ng * sizeof(dev::GroupInfo)) != hipSuccess ||
+            (W > 128 && dev_alloc(&h->d_tile_bits, ng * 4 * h->ds.tiles128) != hipSuccess))
+            return bail(fail(IBP_ENOMEM, "device allocation for metadata failed"));
     }
     if ((d.flags & IBP_STREAM_PARTICIPATION) && d.n_rows > 0 && d.n_rows <= ~0ull / dev::kRowLineRows &&
         (uint64_t)d.row_bytes * dev::kRowLineRows <= 0xFFFF) {

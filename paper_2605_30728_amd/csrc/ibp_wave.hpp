@@ -181,9 +181,25 @@ __device__ __forceinline__ void load_window(__amdgpu_buffer_rsrc_t r, uint32_t q
 // Store of a gathered output word that no later step of the kernel reads: marked
 // non-temporal, so a gather's output stream does not evict the metadata slots and packed
 // rows that neighbouring requests are about to read from L2 (measured: 7% on 53k Zipf
-// lookups, whose hot rows repeat across waves; the contiguous decompress keeps plain
-// stores, which measured 7% faster there).
+// lookups, whose hot rows repeat across waves).
 __device__ __forceinline__ void store_out(uint32_t *p, uint32_t v) { __builtin_nontemporal_store(v, p); }
+
+// N neighbouring words in one non-temporal store through a descriptor (row_rsrc) over their
+// output row, whose range check drops the words past it.
+template <int N>
+__device__ __forceinline__ void store_words(__amdgpu_buffer_rsrc_t r, uint32_t byte, const uint32_t (&v)[N]) {
+    constexpr int kNonTemporal = 2;   // the instruction's cache policy bits
+    if constexpr (N == 1) {
+        __builtin_amdgcn_raw_buffer_store_b32(v[0], r, (int)byte, 0, kNonTemporal);
+    } else {
+        typedef uint32_t vec __attribute__((ext_vector_type(N)));
+        vec x;
+#pragma unroll
+        for (int k = 0; k < N; ++k) x[k] = v[k];
+        if constexpr (N == 2) __builtin_amdgcn_raw_buffer_store_b64(x, r, (int)byte, 0, kNonTemporal);
+        else __builtin_amdgcn_raw_buffer_store_b128(x, r, (int)byte, 0, kNonTemporal);
+    }
+}
 
 // Maximum over the 64 lanes of a wave (DPP, as the scan), result in every lane's SGPR.
 __device__ __forceinline__ uint32_t wave_max(uint32_t v) {
