@@ -91,6 +91,12 @@ hipError_t launch_gather_slots(const DevStream &s, const uint8_t *payload, const
                                const uint32_t *soff, uint64_t n, void *out, unsigned long long *err,
                                hipStream_t stream);
 
+// Thresholded-scheme rows of at most 128 words, contiguous (ids and sg null) or gathered
+// (ibp_part_kernels.hip); arguments as the two above.
+hipError_t launch_part_narrow(const DevStream &s, const uint8_t *payload, uint64_t pay_base, const int64_t *ids,
+                              const uint32_t *sg, const uint32_t *soff, uint64_t first, uint64_t n, void *out,
+                              unsigned long long *err, hipStream_t stream);
+
 // Fills groups[0..n_groups) (from s.meta, s.index and s.row_align) and, unless null, the
 // tile_bits table (n_groups * s.tiles128 entries) of a clustered-scheme stream.
 hipError_t launch_group_info(const DevStream &s, GroupInfo *groups, uint32_t *tile_bits, hipStream_t stream);

@@ -60,10 +60,6 @@ __device__ __forceinline__ uint32_t own_lane() {
     return l;
 }
 
-// Keeps the loads above it above the rebuilds below it (they would else be sunk to their
-// first use, behind other items' stores). No instruction.
-__device__ __forceinline__ void keep_order() { asm volatile("" ::: "memory"); }
-
 // f(integral_constant<int, i>) for i in [A, B): every index a constant, so that what is
 // kept per item stays in registers.
 template <int A, int B, class F>

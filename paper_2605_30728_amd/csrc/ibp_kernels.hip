@@ -27,6 +27,7 @@
 #include <type_traits>
 
 #include "ibp_device.hpp"
+#include "ibp_tile.hpp"
 #include "ibp_wave.hpp"
 
 namespace ibp {
@@ -34,98 +35,6 @@ namespace dev {
 
 namespace {
 
-
-// Per-wave decode state for one tile of a row (64*K words) of one cluster.
-template <int K, int MAXR>
-struct Tile {
-    uint32_t bv[K];          // Bitval of the lane's words
-    uint32_t nm[K];          // ~Mask: the variant positions
-    uint32_t s[K];           // bit offset of the word inside the packed row
-    uint32_t pk[K];          // packed width popcount(~Mask) (0 past the row's end)
-    uint32_t rot[K][MAXR];   // rotate-right amount that lands run k at its position
-    uint32_t rm[K][MAXR];    // run k's bits in place
-    uint32_t bits;           // packed bits of this tile (wave-uniform)
-    int nr;                  // runs applied per word (uniform); -1 = generic loop
-};
-
-template <int K, int MAXR>
-__device__ __forceinline__ void tile_setup(Tile<K, MAXR> &t, const uint32_t *__restrict__ mg,
-                                           uint32_t W, uint32_t w0, uint32_t carry) {
-    const uint32_t l = lane_id();
-    uint32_t c = carry;
-#pragma unroll
-    for (int j = 0; j < K; ++j) {
-        const uint32_t w = w0 + l + kWave * j;
-        uint32_t m = 0xFFFFFFFFu, b = 0u;
-        if (w < W) {
-            m = mg[w];
-            b = mg[W + w];
-        }
-        t.nm[j] = ~m;
-        t.bv[j] = b;
-        const uint32_t n = (uint32_t)__builtin_popcount(~m);
-        t.pk[j] = n;
-        const uint32_t inc = wave_incl_scan(n);
-        t.s[j] = c + inc - n;
-        c += (uint32_t)__builtin_amdgcn_readlane((int)inc, 63);
-    }
-    t.bits = c - carry;
-
-    int cnt_max = 0;
-    bool rest = false;
-#pragma unroll
-    for (int j = 0; j < K; ++j) {
-        uint32_t v = t.nm[j];
-        uint32_t so = 0;
-        int cnt = 0;
-#pragma unroll
-        for (int k = 0; k < MAXR; ++k) {
-            const uint32_t low = v & (0u - v);
-            const uint32_t tt = v + low;      // carries through the lowest run
-            const uint32_t run = v & ~tt;
-            v &= tt;
-            const uint32_t lo = (uint32_t)__builtin_ctz(run | 0x80000000u);
-            t.rot[j][k] = (so - lo) & 31u;
-            t.rm[j][k] = run;
-            so += (uint32_t)__builtin_popcount(run);
-            cnt += run != 0u;
-        }
-        cnt_max = cnt > cnt_max ? cnt : cnt_max;
-        rest = rest || v != 0u;
-    }
-    if (__any(rest)) {
-        t.nr = -1;
-    } else {
-        int nr = 0;
-#pragma unroll
-        for (int k = 0; k < MAXR; ++k)
-            if (__any(cnt_max > k)) nr = k + 1;
-        t.nr = nr;
-    }
-}
-
-// Rebuild one word from its 32-bit window x: Bitval | the NR runs of variant bits.
-template <int NR, int K, int MAXR>
-__device__ __forceinline__ uint32_t word_fast(const Tile<K, MAXR> &t, int j, uint32_t x) {
-    uint32_t acc = t.bv[j];
-#pragma unroll
-    for (int k = 0; k < NR; ++k) acc |= __builtin_amdgcn_alignbit(x, x, t.rot[j][k]) & t.rm[j][k];
-    return acc;
-}
-
-// Generic rebuild for any Mask: walk the runs of ~Mask from the lowest bit up.
-__device__ __forceinline__ uint32_t word_generic(uint32_t bv, uint32_t nm, uint32_t x) {
-    uint32_t acc = bv, v = nm;
-    while (v) {
-        const uint32_t low = v & (0u - v);
-        const uint32_t tt = v + low;
-        const uint32_t run = v & ~tt;
-        v &= tt;
-        acc |= (x << __builtin_ctz(run)) & run;
-        x = __builtin_amdgcn_alignbit(0u, x, (uint32_t)__builtin_popcount(run));
-    }
-    return acc;
-}
 
 // Decode rows 0 .. min(RB, n) - 1 of one cluster (n >= RB unless PART). `at.byte(i)` is the
 // payload byte where row i's packed bits start and `at.out(i)` the row's output; both are
@@ -665,26 +574,6 @@ __device__ __forceinline__ uint32_t part_tile_any(const Tile<K, MAXR> &t, const 
     return part_tile<-1>(t, pay32, rbyte, raw, m, start, W, w0, orow);
 }
 
-// Payload byte span [o0, o1) of row r of a participation-scheme stream. With line-packed
-// offsets a request reads one 128-byte line (its 60-row block's base offset and the u16
-// ends of the block's rows) instead of two u64 entries in the per-row index: sparse
-// requests then share lines 7.5 times more often.
-__device__ __forceinline__ void row_span(const DevStream &s, uint64_t r, uint64_t &o0, uint64_t &o1) {
-    if (s.row_lines) {
-        const uint64_t j = __umul64hi(r, s.rl_magic);
-        const uint32_t k = (uint32_t)(r - j * kRowLineRows);
-        const uint8_t *__restrict__ ln = s.row_lines + j * 128ull;
-        const uint64_t base = *reinterpret_cast<const uint64_t *>(ln);
-        const uint16_t *__restrict__ ends = reinterpret_cast<const uint16_t *>(ln + 8);
-        const uint32_t start = ends[k ? k - 1u : 0u];
-        o0 = base + (k ? start : 0u);
-        o1 = base + ends[k];
-    } else {
-        o0 = s.index[r];
-        o1 = s.index[r + 1];
-    }
-}
-
 // One wave decodes `per_wave` consecutive work items (rows of a range, requests of a
 // gather), one row at a time.
 template <int K, int MAXR, int SRC>
@@ -768,14 +657,6 @@ struct PartLoads {
     uint32_t d0[RB][K], d1[RB][K];
     uint32_t bs[RB][K];   // bits 0-4: the window's shift; bits 5-31: all ones when the chunk is compressed
 };
-
-// m ? a : b, bit by bit, in one instruction (written out, the compiler splits it into a
-// not, an and and an and-or, and keeps every row's inverted mask live)
-__device__ __forceinline__ uint32_t bit_select(uint32_t m, uint32_t a, uint32_t b) {
-    uint32_t r;
-    asm("v_bfi_b32 %0, %1, %2, %3" : "=v"(r) : "v"(m), "v"(a), "v"(b));
-    return r;
-}
 
 template <int RB, int PRE, int K, int MAXR>
 __device__ __forceinline__ void part_batch_load(const Tile<K, MAXR> &t, const uint32_t *__restrict__ pay32,
@@ -998,7 +879,8 @@ __device__ __forceinline__ void part_mixed_batch(const DevStream &s, const uint3
     }
 }
 
-// Participation-scheme rows that fit one tile (W <= 64K), in batches of RB rows. With
+// Participation-scheme rows of 129 to 512 words (narrower ones: ibp_part_kernels.hip), one
+// tile each, in batches of RB rows. With
 // DEFER (two batches per wave) each batch's stores wait until the next batch's window
 // loads have left; otherwise a batch stores at once and keeps fewer registers. A wave owns
 // `seg` (<= 64) work items; lane i < seg first locates item i (its cluster, the first data
@@ -1006,7 +888,7 @@ __device__ __forceinline__ void part_mixed_batch(const DevStream &s, const uint3
 // Mask, ONE) is decoded with that cluster's tile; a batch of rows from different clusters
 // loads each row's Mask/Bitval words (part_mixed_batch).
 template <int K, int MAXR, int RB, int SRC, int PRE, bool DEFER, bool ONE>
-__global__ __launch_bounds__(kBlock, (ONE && (K == 1 || (K == 2 && PRE != 0))) ? 8 : 1) void k_part_batched(DevStream s, const uint32_t *__restrict__ pay32,
+__global__ __launch_bounds__(kBlock) void k_part_batched(DevStream s, const uint32_t *__restrict__ pay32,
                                                           uint64_t pay_base, const int64_t *__restrict__ ids,
                                                           const uint32_t *__restrict__ sg,
                                                           const uint32_t *__restrict__ soff, uint64_t first,
@@ -1121,11 +1003,10 @@ hipError_t launch_part_k(const DevStream &s, const uint32_t *p, uint64_t pay_bas
                          const uint32_t *sg, const uint32_t *soff, uint64_t first, uint64_t n, uint32_t *o,
                          unsigned long long *err, hipStream_t stream) {
     if (s.W <= (uint32_t)(kWave * K)) {
-        // rows of one tile: batches of RB rows, 1-2 batches per wave (2 when there is work
-        // for ~16k waves; measured on the KV layer: 4 batches 57.6 us, 2 batches 54.1, 8
-        // batches 64.4: a wave's lookup and its batches are dependent round trips, and more
-        // waves in flight hide them better than more batches per wave)
-        constexpr int RB = K <= 1 ? 8 : (K <= 2 ? 4 : (K <= 4 ? 2 : 1));
+        // rows of one tile of 129 to 512 words: batches of RB rows, 1-2 batches per wave (2
+        // when there is work for ~16k waves: a wave's lookup and its batches are dependent
+        // round trips, and more waves in flight hide them better than more batches per wave)
+        constexpr int RB = K <= 4 ? 2 : 1;
         const uint32_t nb = (uint32_t)std::max<uint64_t>(1, std::min<uint64_t>(2, n / (16384ull * RB)));
         const uint32_t seg = RB * nb;
         if (seg > (uint32_t)kWave) return hipErrorInvalidValue;   // lane i holds item i
@@ -1135,7 +1016,6 @@ hipError_t launch_part_k(const DevStream &s, const uint32_t *p, uint64_t pay_bas
         // at most 64, else loaded per batch
         const uint32_t chunks = s.W / s.part_m;
         const int pre = chunks <= 32u ? 1 : (chunks <= 64u ? 2 : 0);
-        if (K == 1 && pre == 0) return hipErrorInvalidValue;   // W <= 64 words: at most 64 chunks
         const bool one = (uint64_t)s.G >= s.n_rows;   // a single cluster
         auto go = [&](auto pre_tag, auto defer_tag) {
             constexpr int P = decltype(pre_tag)::value;
@@ -1158,17 +1038,11 @@ hipError_t launch_part_k(const DevStream &s, const uint32_t *p, uint64_t pay_bas
         auto go_pre = [&](auto defer_tag) {
             if (pre == 1) go(std::integral_constant<int, 1>{}, defer_tag);
             else if (pre == 2) go(std::integral_constant<int, 2>{}, defer_tag);
-            else if constexpr (K > 1) go(std::integral_constant<int, 0>{}, defer_tag);   // K = 1: at most 64 chunks
+            else go(std::integral_constant<int, 0>{}, defer_tag);
         };
-        // deferred stores, measured: the KV layer (K = 1) 4% faster, 1 KB rows read in place
-        // from host memory (K = 4) 5-25% faster; at K = 2 their registers cost a wave per
-        // SIMD and the GNN gather ran 15% slower
-        if constexpr (K != 2) {
-            if (nb > 1) go_pre(std::true_type{});
-            else go_pre(std::false_type{});
-        } else {
-            go_pre(std::false_type{});
-        }
+        // deferred stores, measured: 1 KB rows read in place from host memory 5-25% faster
+        if (nb > 1) go_pre(std::true_type{});
+        else go_pre(std::false_type{});
         return hipGetLastError();
     }
     // rows of several tiles (only at eight words per lane): one row at a time per wave
@@ -1229,9 +1103,8 @@ hipError_t launch_part(const DevStream &s_in, const uint8_t *payload, uint64_t p
     // slower through the lines, the GNN minibatch even)
     DevStream s = s_in;
     if (!ids || n * kRowLineRows < s.n_rows) s.row_lines = nullptr;
+    if (s.W <= 128) return launch_part_narrow(s, payload, pay_base, ids, sg, soff, first, n, out, err, stream);
     switch (words_per_lane(s.W)) {
-    case 1: return launch_part_k<1, 4>(s, p, pay_base, ids, sg, soff, first, n, o, err, stream);
-    case 2: return launch_part_k<2, 4>(s, p, pay_base, ids, sg, soff, first, n, o, err, stream);
     case 4: return launch_part_k<4, 2>(s, p, pay_base, ids, sg, soff, first, n, o, err, stream);
     default: return launch_part_k<8, 1>(s, p, pay_base, ids, sg, soff, first, n, o, err, stream);
     }

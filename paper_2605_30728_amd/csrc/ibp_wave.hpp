@@ -160,6 +160,10 @@ __device__ __forceinline__ void row_window(__amdgpu_buffer_rsrc_t r, uint32_t bi
     }
 }
 
+// Keeps the loads above it above the rebuilds below it (they would else be sunk to their
+// first use, behind other items' stores). No instruction.
+__device__ __forceinline__ void keep_order() { asm volatile("" ::: "memory"); }
+
 // A word's 64-bit window as two dword loads (dwords q and q + 1 of p). The compiler would
 // merge them into one 8-byte load, which is misaligned for every odd q; an opaque second
 // index keeps them two 4-byte loads. Measured: the 111M-row gather 830 -> 695 us, the bf16
@@ -251,6 +255,34 @@ __device__ __forceinline__ uint32_t word_deposit(uint32_t bv, uint32_t nm, uint3
         y = (y & below) | ((y << width) & ~below);
     }
     return (nm & y) | (~nm & bv);
+}
+
+// m ? a : b, bit by bit, in one instruction (written out, the compiler splits it into a
+// not, an and and an and-or, and keeps every row's inverted mask live)
+__device__ __forceinline__ uint32_t bit_select(uint32_t m, uint32_t a, uint32_t b) {
+    uint32_t r;
+    asm("v_bfi_b32 %0, %1, %2, %3" : "=v"(r) : "v"(m), "v"(a), "v"(b));
+    return r;
+}
+
+// Payload byte span [o0, o1) of row r of a participation-scheme stream. With line-packed
+// offsets a request reads one 128-byte line (its 60-row block's base offset and the u16
+// ends of the block's rows) instead of two u64 entries in the per-row index: sparse
+// requests then share lines 7.5 times more often.
+__device__ __forceinline__ void row_span(const DevStream &s, uint64_t r, uint64_t &o0, uint64_t &o1) {
+    if (s.row_lines) {
+        const uint64_t j = __umul64hi(r, s.rl_magic);
+        const uint32_t k = (uint32_t)(r - j * kRowLineRows);
+        const uint8_t *__restrict__ ln = s.row_lines + j * 128ull;
+        const uint64_t base = *reinterpret_cast<const uint64_t *>(ln);
+        const uint16_t *__restrict__ ends = reinterpret_cast<const uint16_t *>(ln + 8);
+        const uint32_t start = ends[k ? k - 1u : 0u];
+        o0 = base + (k ? start : 0u);
+        o1 = base + ends[k];
+    } else {
+        o0 = s.index[r];
+        o1 = s.index[r + 1];
+    }
 }
 
 // Exclusive bit offsets of the lane's words inside a packed row (word order t + 64*j)
