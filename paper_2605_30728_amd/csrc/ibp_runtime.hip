@@ -53,6 +53,12 @@ constexpr uint64_t kStageBytes = 128ull << 20;   // one staging buffer (a whole 
                                                   // against 0.85 in two 64 MiB copies)
 constexpr int kStages = 3;                        // staging buffers in rotation
 constexpr int kIdSlots = 2;                       // host-id buffers in rotation
+// Host ids of a gather: up to this many are read by the kernel in the pinned slot they were
+// staged in, more are copied to the device first. Measured (us, copied -> in place): 208 ids
+// 14.4 -> 11.4, 4,160 22.2 -> 12.2, 16,640 24.6 -> 15.2, 53,248 34.5 -> 27.8, 163,840 77.6 ->
+// 76 (a copy costs a call and ~8 us of latency before the kernel; in place, a wave's 64 bytes
+// of ids cross PCIe as a 128-byte line, twice the bytes).
+constexpr uint64_t kIdsInPlace = 65536;
 constexpr uint64_t kRowAlign = 128;               // PCIe line: row start of aligned zero-copy
 constexpr uint64_t kMaxRuns = 4096;               // copy pieces of a line-aligned cluster layout
 constexpr uint64_t kCountBytes = dev::kCountLines * dev::kCountStride * 8;   // cache counters
@@ -208,7 +214,8 @@ struct ibp_handle {
     // host ids of gathers over a device or zero-copy payload: two slots alternate, so the
     // ids of call k+1 are staged while the kernel of call k still reads slot k%2
     int64_t *h_ids[kIdSlots] = {}, *d_ids[kIdSlots] = {};
-    uint64_t ids_cap[kIdSlots] = {};
+    const int64_t *h_ids_dev[kIdSlots] = {};   // the device's address of h_ids
+    uint64_t ids_cap[kIdSlots] = {}, d_ids_cap[kIdSlots] = {};
     hipEvent_t ev_ids_free[kIdSlots] = {};
     bool ids_used[kIdSlots] = {};
     int next_ids = 0;
@@ -327,6 +334,7 @@ void release_handle(ibp_handle *h) {
         h->h_ids[j] = nullptr;
         h->ev_ids_free[j] = nullptr;
         h->ids_cap[j] = 0;
+        h->d_ids_cap[j] = 0;
     }
     pinned_free(h->h_payload);
     h->h_payload = nullptr;
@@ -360,24 +368,39 @@ void free_handle(ibp_handle *h) {
 }
 
 // Claim id slot j for n ids: its last kernel must have finished with it (host wait, needed
-// anyway before the pinned half is rewritten), and the buffers must hold n ids.
+// anyway before the pinned half is rewritten), and the buffers must hold n ids (the device
+// half only when the ids are copied).
 ibp_status claim_ids(ibp_handle *h, int j, uint64_t n) {
     if (h->ids_used[j]) IBP_HIP(h, wait_event(h->ev_ids_free[j]));
-    if (n <= h->ids_cap[j]) return IBP_OK;
-    uint64_t cap = std::max<uint64_t>(n, 2 * h->ids_cap[j]);
-    pinned_free(h->h_ids[j]);
-    dev_free(h->d_ids[j]);
-    h->h_ids[j] = nullptr;
-    h->d_ids[j] = nullptr;
-    h->ids_cap[j] = 0;
-    if (pinned_alloc(&h->h_ids[j], cap * 8) != hipSuccess)
-        return fail(IBP_ENOMEM, "pinned allocation for row ids failed");
-    if (dev_alloc(&h->d_ids[j], cap * 8) != hipSuccess) {
-        pinned_free(h->h_ids[j]);      // a failed call holds nothing new
+    if (n > h->ids_cap[j]) {
+        const uint64_t cap = std::max<uint64_t>(n, 2 * h->ids_cap[j]);
+        pinned_free(h->h_ids[j]);
         h->h_ids[j] = nullptr;
-        return fail(IBP_ENOMEM, "device allocation for row ids failed");
+        h->ids_cap[j] = 0;
+        if (pinned_alloc(&h->h_ids[j], cap * 8) != hipSuccess)
+            return fail(IBP_ENOMEM, "pinned allocation for row ids failed");
+        void *dp = nullptr;
+        const hipError_t e = hipHostGetDevicePointer(&dp, h->h_ids[j], 0);
+        if (e != hipSuccess) {
+            pinned_free(h->h_ids[j]);      // a failed call holds nothing new
+            h->h_ids[j] = nullptr;
+            return hip_fail(h, e, "hipHostGetDevicePointer");
+        }
+        h->h_ids_dev[j] = static_cast<const int64_t *>(dp);
+        h->ids_cap[j] = cap;
     }
-    h->ids_cap[j] = cap;
+    if (n > kIdsInPlace && n > h->d_ids_cap[j]) {
+        dev_free(h->d_ids[j]);
+        h->d_ids[j] = nullptr;
+        h->d_ids_cap[j] = 0;
+        if (dev_alloc(&h->d_ids[j], h->ids_cap[j] * 8) != hipSuccess) {
+            pinned_free(h->h_ids[j]);
+            h->h_ids[j] = nullptr;
+            h->ids_cap[j] = 0;
+            return fail(IBP_ENOMEM, "device allocation for row ids failed");
+        }
+        h->d_ids_cap[j] = h->ids_cap[j];
+    }
     return IBP_OK;
 }
 
@@ -946,8 +969,12 @@ ibp_status gather_impl(ibp_handle *h, const int64_t *row_ids, uint64_t n_ids, vo
         if (st != IBP_OK) return st;
         h->next_ids = (j + 1) % kIdSlots;
         std::memcpy(h->h_ids[j], row_ids, n_ids * 8);
-        IBP_HIP(h, hipMemcpyAsync(h->d_ids[j], h->h_ids[j], n_ids * 8, hipMemcpyHostToDevice, s));
-        IBP_HIP(h, dev::launch_gather(h->ds, h->k_payload, h->d_ids[j], nullptr, nullptr, n_ids, d_out, h->d_err, s));
+        const int64_t *ids = h->h_ids_dev[j];   // (the slot is not rewritten before ev_ids_free)
+        if (n_ids > kIdsInPlace) {
+            IBP_HIP(h, hipMemcpyAsync(h->d_ids[j], h->h_ids[j], n_ids * 8, hipMemcpyHostToDevice, s));
+            ids = h->d_ids[j];
+        }
+        IBP_HIP(h, dev::launch_gather(h->ds, h->k_payload, ids, nullptr, nullptr, n_ids, d_out, h->d_err, s));
         IBP_HIP(h, hipEventRecord(h->ev_ids_free[j], s));
         h->ids_used[j] = true;
         h->stats.h2d_bytes += n_ids * 8;

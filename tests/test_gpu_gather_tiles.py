@@ -109,3 +109,25 @@ def test_sixteen_pairs(torch, W):
         ibp.ibp_gather_decompress_device(h, torch.from_numpy(ids).cuda(), out)
         torch.cuda.synchronize()
         assert np.array_equal(out.cpu().numpy().reshape(-1, L), rows[ids])
+
+
+def test_host_ids_in_place_and_copied(torch):
+    """Host ids read in their pinned slot (at most 65,536) or copied to the device first, in
+    calls that follow one another without a wait, so that each slot is taken again while
+    earlier calls may still read it."""
+    n, L, G = 5000, 64, 32
+    rows = rows_of_runs(L // 4, n, G, KINDS["two"], seed=5)
+    rng = np.random.default_rng(5)
+    counts = [3, 65536, 65537, 1, 40000, 65535, 70000, 8, 9]
+    with ibp.ibp_open(oracle.compress(rows, G), 0) as h:
+        calls = []
+        for c in counts:
+            ids = rng.integers(0, n, size=c).astype(np.int64)
+            out = torch.empty(c * L, dtype=torch.uint8, device="cuda")
+            sent = ids.copy()
+            ibp.ibp_gather_decompress(h, sent, out)
+            sent[:] = -1                       # read before the call returned
+            calls.append((ids, out))
+        torch.cuda.synchronize()
+        for ids, out in calls:
+            assert np.array_equal(out.cpu().numpy().reshape(-1, L), rows[ids]), ids.size
