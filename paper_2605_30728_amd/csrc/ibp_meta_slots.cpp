@@ -78,9 +78,10 @@ uint32_t cluster_pairs(const uint8_t *mg, uint32_t W, uint32_t *pm, uint32_t *pb
 uint32_t build_meta_slots(const uint8_t *meta, uint64_t n_groups, uint32_t W, uint32_t K, Pool &pool,
                           std::vector<uint8_t> &slots, bool word_order) {
     const uint64_t raw = 8ull * W;
+    const uint64_t block = std::max<uint64_t>(1, 16384 / W);   // ~16k words: few wide clusters are shared out too
     // pass 1: the most distinct pairs of any cluster
     std::atomic<uint32_t> most{0};
-    pool.run(n_groups, 1024, [&](uint64_t lo, uint64_t hi) {
+    pool.run(n_groups, block, [&](uint64_t lo, uint64_t hi) {
         uint32_t pm[kMaxPairs], pb[kMaxPairs], m = 0;
         for (uint64_t g = lo; g < hi && m <= kMaxPairs; ++g)
             m = std::max(m, cluster_pairs(meta + g * raw, W, pm, pb, nullptr));
@@ -96,7 +97,7 @@ uint32_t build_meta_slots(const uint8_t *meta, uint64_t n_groups, uint32_t W, ui
     const uint64_t S = word_order ? meta_slot_bytes_of(P, W) : meta_slot_bytes(P, K);
     slots.assign(std::max<uint64_t>(n_groups, 1) * S, 0);
     // pass 2: the slots
-    pool.run(n_groups, 1024, [&](uint64_t lo, uint64_t hi) {
+    pool.run(n_groups, block, [&](uint64_t lo, uint64_t hi) {
         std::vector<uint8_t> word_pair(W);
         uint32_t pm[kMaxPairs], pb[kMaxPairs];
         for (uint64_t g = lo; g < hi; ++g) {
