@@ -236,7 +236,16 @@ def ibp_compress(rows, group_rows, n_threads=0):
     bound = ibp_compress_bound(n_rows, row_bytes, group_rows)
     got = _u64(0)
     L = lib()
-    # size first (out_cap 0 reports the size), then the real call
+    # into a buffer of the largest size, of which only the stream's pages are ever touched;
+    # if that much address space is not to be had, size first (out_cap 0 reports the size)
+    try:
+        out = np.empty(bound, np.uint8)
+    except MemoryError:
+        out = None
+    if out is not None:
+        _check(L.ibp_compress(a.ctypes.data, n_rows, row_bytes, group_rows, n_threads, out.ctypes.data, bound,
+                              ctypes.byref(got)), "ibp_compress")
+        return out[:got.value]
     st = L.ibp_compress(a.ctypes.data, n_rows, row_bytes, group_rows, n_threads, None, 0, ctypes.byref(got))
     if st not in (IBP_OK, IBP_ENOMEM) or (st == IBP_ENOMEM and got.value == 0 and n_rows > 0):
         _check(st, "ibp_compress")
