@@ -5,12 +5,15 @@
 // requested id against the table: hits are decoded from the slab in HBM, misses from the
 // stream's payload in pinned host memory, read in place over PCIe.
 //
-// The decode is the clustered-scheme gather: one wave per batch of RB requests, each row
+// Rows of at most 128 words whose clusters have metadata slots are decoded by the gather of
+// ibp_gather_kernels.hip, which finds a row here before its payload offset. The others by the
+// kernel below, as the row-at-a-time gather: one wave per batch of RB requests, each row
 // decoded on its own (its cluster's Mask/Bitval, a scan of popcount(~Mask), the holes
 // deposit), all loads of the batch issued before any word is rebuilt. The only change is
 // that a row's packed bytes are located by an absolute address chosen per request.
 #include <type_traits>
 
+#include "ibp_cache.hpp"
 #include "ibp_device.hpp"
 #include "ibp_wave.hpp"
 
@@ -18,11 +21,6 @@ namespace ibp {
 namespace dev {
 
 namespace {
-
-struct Slot {
-    uint64_t key;   // row id + 1; 0 = empty
-    uint64_t val;   // cache entry
-};
 
 template <int K, int RB, int FORM>
 __global__ __launch_bounds__(kBlock) void k_cache_gather(DevStream s, CacheView c, const int64_t *__restrict__ ids,
@@ -41,37 +39,17 @@ __global__ __launch_bounds__(kBlock) void k_cache_gather(DevStream s, CacheView 
     const uint64_t uid = valid ? (uint64_t)id : 0;
     const uint64_t g_l = s.G == 1 ? uid : __umul64hi(uid, s.g_magic);
     const uint32_t r_l = (uint32_t)(uid - g_l * s.G);
-    bool hit = false;
-    uint64_t val = 0;
-    if (valid) {
-        const Slot *__restrict__ tab = reinterpret_cast<const Slot *>(c.table);
-        const uint64_t key = uid + 1;
-        uint64_t h = (uid * 0x9E3779B97F4A7C15ull) >> (64 - c.log2cap);
-        // the table is at most half full, so an empty slot ends every probe sequence
-        for (uint64_t k = 0; k <= c.mask; ++k) {
-            const Slot e = tab[h];
-            if (e.key == key) {
-                hit = true;
-                val = e.val;
-                break;
-            }
-            if (e.key == 0) break;
-            h = (h + 1) & c.mask;
-        }
-    }
     // byte address of the row's packed bits: the slab entry for a hit; for a miss the
     // cluster's payload offset, to which the row's index times its packed size is added
     // once the size is known from the Mask
-    const uint64_t off_l = hit ? (val & 0xFFFFFFFFFFull) : s.index[g_l];
+    uint64_t off_l = 0;
+    const bool hit = valid && cache_probe(c, uid, off_l);
+    if (!hit) off_l = s.index[g_l];
     const uint32_t mul_l = hit ? 0u : r_l;
     const uint64_t nhit = __ballot(valid && hit), nmiss = __ballot(valid && !hit);
     const uint64_t bad = __ballot(l < cnt && !valid);
     if (l == 0) {
-        // counters spread over kCountLines 128-byte lines so that waves do not all
-        // contend for one address
-        unsigned long long *cnt = c.counts + (blockIdx.x % kCountLines) * kCountStride;
-        if (nhit) atomicAdd(cnt, (unsigned long long)__popcll(nhit));
-        if (nmiss) atomicAdd(cnt + 1, (unsigned long long)__popcll(nmiss));
+        cache_count(c, (uint32_t)__popcll(nhit), (uint32_t)__popcll(nmiss));
         if (bad) atomicAdd(err, (unsigned long long)__popcll(bad));
     }
     uint32_t *__restrict__ out_seg = out + i0 * W;
@@ -146,12 +124,15 @@ __global__ __launch_bounds__(kBlock) void k_cache_gather(DevStream s, CacheView 
 hipError_t launch_cache_gather(const DevStream &s, const CacheView &c, const int64_t *ids, uint64_t n, void *out,
                                unsigned long long *err, hipStream_t stream) {
     if (n == 0) return hipSuccess;
+    if (s.slots && s.word_order)
+        return launch_gather_slots(s, &c, c.host_payload, ids, nullptr, nullptr, n, out, err, stream);
     auto *o = static_cast<uint32_t *>(out);
     auto grid = [&](uint64_t rb) { return dim3((unsigned)(((n + rb - 1) / rb + kWavesPerBlock - 1) / kWavesPerBlock)); };
     auto go = [&](auto kk, auto rb) {
         constexpr int KK = decltype(kk)::value, R = decltype(rb)::value;
-        if (s.slots) hipLaunchKernelGGL((k_cache_gather<KK, R, kMetaSlots>), grid(R), dim3(kBlock), 0, stream, s, c, ids, n, o, err);
-        else hipLaunchKernelGGL((k_cache_gather<KK, R, kMetaRaw>), grid(R), dim3(kBlock), 0, stream, s, c, ids, n, o, err);
+        if (s.slots) {   // (lane order: rows of more than 128 words)
+            if constexpr (KK >= 4) hipLaunchKernelGGL((k_cache_gather<KK, R, kMetaSlots>), grid(R), dim3(kBlock), 0, stream, s, c, ids, n, o, err);
+        } else hipLaunchKernelGGL((k_cache_gather<KK, R, kMetaRaw>), grid(R), dim3(kBlock), 0, stream, s, c, ids, n, o, err);
     };
     if (s.W <= 64) go(std::integral_constant<int, 1>{}, std::integral_constant<int, 8>{});
     else if (s.W <= 128) go(std::integral_constant<int, 2>{}, std::integral_constant<int, 4>{});

@@ -85,12 +85,6 @@ hipError_t launch_gather(const DevStream &s, const uint8_t *payload, const int64
                          const uint32_t *sg, const uint32_t *soff, uint64_t n, void *out,
                          unsigned long long *err, hipStream_t stream);
 
-// The same gather for streams with word-order slots and the payload (or the stage) in device
-// memory (ibp_gather_kernels.hip); launch_gather sends those here.
-hipError_t launch_gather_slots(const DevStream &s, const uint8_t *payload, const int64_t *ids, const uint32_t *sg,
-                               const uint32_t *soff, uint64_t n, void *out, unsigned long long *err,
-                               hipStream_t stream);
-
 // Thresholded-scheme rows of at most 128 words, contiguous (ids and sg null) or gathered
 // (ibp_part_kernels.hip); arguments as the two above.
 hipError_t launch_part_narrow(const DevStream &s, const uint8_t *payload, uint64_t pay_base, const int64_t *ids,
@@ -119,6 +113,13 @@ struct CacheView {
 // found in the cache table are decoded from the slab, the others from the pinned host
 // payload; ids outside [0, n_rows) give a zero row and one increment of *err.
 hipError_t launch_cache_gather(const DevStream &s, const CacheView &c, const int64_t *ids, uint64_t n, void *out,
+                               unsigned long long *err, hipStream_t stream);
+
+// The two gathers above for streams with word-order slots (ibp_gather_kernels.hip):
+// launch_gather and launch_cache_gather (cache non-null, payload its host payload) send those
+// here. A payload in host memory, or behind a cache, only with rows of at most 128 words.
+hipError_t launch_gather_slots(const DevStream &s, const CacheView *cache, const uint8_t *payload, const int64_t *ids,
+                               const uint32_t *sg, const uint32_t *soff, uint64_t n, void *out,
                                unsigned long long *err, hipStream_t stream);
 
 }  // namespace dev

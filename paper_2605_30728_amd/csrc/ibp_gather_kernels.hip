@@ -1,5 +1,7 @@
-// gfx950 row gather of clustered-scheme streams whose clusters have compact metadata slots,
-// with the packed rows in device memory (the payload, or a staged chunk of it).
+// gfx950 row gather of clustered-scheme streams whose clusters have compact metadata slots:
+// packed rows in device memory (the payload, or a staged chunk of it), and, for rows of at
+// most 128 words, read in place from pinned host memory, directly or behind the compressed
+// row cache.
 //
 // What bounds it: HBM, once the instructions per row are few enough. A packed row is ~200
 // bytes, and a wave that finds its words' bits row by row (k_gather_rows: ~100 vector and ~80
@@ -28,11 +30,14 @@
 // 164k sorted 400-B rows of 2.4M 33.7 -> 25.6 (130 MB of HBM traffic: 5.1 TB/s, a large
 // copy's rate), 1.5M shuffled 512-B rows of 3M 293 -> 235, 16k random 4-KB rows 230 -> 19.4
 // (there each row's 8 KB of Mask/Bitval words are replaced by its cluster's 640-byte slot).
-// Measured and not kept: half the items in flight (+1-8%), plain stores (+6-24%), one
+// From pinned host memory, us: 82k sorted 400-B rows 486 -> 468 (their distinct 128-B lines at
+// the link's 57 GB/s take 469), 53k Zipf lookups behind a cache that misses 16% 62.3 -> 60.9
+// (lines of the misses: 50). Measured and not kept: half the items in flight (+1-8%), plain stores (+6-24%), one
 // 12-byte load per window for K <= 2 (+4-5%) and three 4-byte ones for K = 4 (+17%).
 #include <algorithm>
 #include <type_traits>
 
+#include "ibp_cache.hpp"
 #include "ibp_device.hpp"
 #include "ibp_wave.hpp"
 
@@ -83,13 +88,15 @@ __device__ __forceinline__ uint32_t deposit(const PairDeposit &e, uint32_t x) {
     return bfi(e.nm, y, e.bv);
 }
 
-template <int K, int P, bool STAGED, bool TILED>
-__global__ __launch_bounds__(kBlock, K <= 2 ? 8 : 5) void k_gather_slots(DevStream s, const uint8_t *__restrict__ pay,
-                                                         const int64_t *__restrict__ ids,
-                                                         const uint32_t *__restrict__ sg,
-                                                         const uint32_t *__restrict__ soff, uint64_t n_items,
-                                                         uint32_t tiles, uint64_t tiles_magic,
-                                                         uint32_t *__restrict__ out, unsigned long long *err) {
+enum { kFromIds = 0, kFromStage = 1, kFromCache = 2 };   // where an item's row is found
+
+// SPLIT: a window as separate dword loads.
+template <int K, int P, int SRC, bool TILED, bool SPLIT>
+__device__ __forceinline__ void gather_slots(const DevStream &s, const CacheView &c, const uint8_t *__restrict__ pay,
+                                             const int64_t *__restrict__ ids, const uint32_t *__restrict__ sg,
+                                             const uint32_t *__restrict__ soff, uint64_t n_items, uint32_t tiles,
+                                             uint64_t tiles_magic, uint32_t *__restrict__ out,
+                                             unsigned long long *err) {
     constexpr int IT = kWave / P;                       // items of the wave
     constexpr int GROUP = K <= 2 || IT < 4 ? IT : 4;    // items whose windows are in flight together
     constexpr int H = (K + 1) / 2;                      // windows per lane: one per two words
@@ -110,12 +117,12 @@ __global__ __launch_bounds__(kBlock, K <= 2 ? 8 : 5) void k_gather_slots(DevStre
         r = __umul64hi(item, tiles_magic);
         t = (uint32_t)(item - r * tiles);
     }
-    bool valid = true;
+    bool valid = true, hit = false;
     uint64_t g, byte;
     uint32_t len;
     const uint8_t *slot_l;
     uint2 pair;
-    if constexpr (STAGED) {
+    if constexpr (SRC == kFromStage) {
         g = sg[r];
         byte = soff[r];
         len = soff[r + 1] - (uint32_t)byte;
@@ -131,6 +138,9 @@ __global__ __launch_bounds__(kBlock, K <= 2 ? 8 : 5) void k_gather_slots(DevStre
         const GroupInfo gi = s.groups[g];
         byte = valid ? gi.off + (uint64_t)(uint32_t)(uid - g * s.G) * gi.stride : 0;
         len = valid ? gi.stride : 0u;   // (an invalid id reads nothing)
+        if constexpr (SRC == kFromCache) {
+            if (valid) hit = cache_probe(c, uid, byte);
+        }
     }
     // every item's pair indices of the lane's words, 4 bits each
     const uint8_t *const idx_l = slot_l + 8 * P + (TILED ? t * (32u * K) : 0u);
@@ -146,7 +156,7 @@ __global__ __launch_bounds__(kBlock, K <= 2 ? 8 : 5) void k_gather_slots(DevStre
     if constexpr (TILED) start = s.tile_bits[g * s.tiles128 + t * (K / 2)];
     // where each item's bits are: the dword its row starts in, the dwords of the row, the
     // first bit of the item
-    const uint8_t *const row_l = pay + (byte & ~3ull);
+    const uint8_t *const row_l = (SRC == kFromCache && hit ? c.slab : pay) + (byte & ~3ull);
     const uint32_t bit0 = ((uint32_t)byte & 3u) * 8u;
     // (at least 12 bytes, readable past any row, so that a window's split loads stay ordered
     // against the range)
@@ -154,6 +164,11 @@ __global__ __launch_bounds__(kBlock, K <= 2 ? 8 : 5) void k_gather_slots(DevStre
     const uint32_t first_l = bit0 + start;
     const uint64_t okm = __ballot(valid && own < cnt);
     const uint64_t badm = __ballot(!valid && own < cnt);
+    if constexpr (SRC == kFromCache) {
+        const uint64_t hits = __ballot(hit && own < cnt && l % P == 0);
+        const uint64_t misses = __ballot(valid && !hit && own < cnt && l % P == 0);
+        if (l == 0) cache_count(c, (uint32_t)__popcll(hits), (uint32_t)__popcll(misses));
+    }
 
     // the deposit of this lane's pair
     const uint32_t nm = ~pair.x;
@@ -208,7 +223,7 @@ __global__ __launch_bounds__(kBlock, K <= 2 ? 8 : 5) void k_gather_slots(DevStre
     auto windows = [&](uint32_t i, const uint32_t (&first)[H], uint32_t (&d)[H][D]) {
         const __amdgpu_buffer_rsrc_t rr = row_of(i);
 #pragma unroll
-        for (int h = 0; h < H; ++h) row_window<D, K <= 2>(rr, first[h], d[h]);
+        for (int h = 0; h < H; ++h) row_window<D, SPLIT>(rr, first[h], d[h]);
     };
     auto words_of = [&](auto how, uint32_t bits, uint32_t i, const uint32_t (&first)[H], const uint32_t (&d)[H][D],
                         uint32_t (&v)[K]) {
@@ -295,6 +310,26 @@ __global__ __launch_bounds__(kBlock, K <= 2 ? 8 : 5) void k_gather_slots(DevStre
     }
 }
 
+template <int K, int P, int SRC, bool TILED, bool SPLIT>
+__global__ __launch_bounds__(kBlock, K <= 2 ? 8 : 5) void k_gather_slots(DevStream s, const uint8_t *__restrict__ pay,
+                                                                         const int64_t *__restrict__ ids,
+                                                                         const uint32_t *__restrict__ sg,
+                                                                         const uint32_t *__restrict__ soff,
+                                                                         uint64_t n_items, uint32_t tiles,
+                                                                         uint64_t tiles_magic,
+                                                                         uint32_t *__restrict__ out,
+                                                                         unsigned long long *err) {
+    gather_slots<K, P, SRC, TILED, SPLIT>(s, CacheView{}, pay, ids, sg, soff, n_items, tiles, tiles_magic, out, err);
+}
+
+template <int K, int P>
+__global__ __launch_bounds__(kBlock, 8) void k_cache_gather_slots(DevStream s, CacheView c,
+                                                                  const int64_t *__restrict__ ids, uint64_t n_items,
+                                                                  uint32_t *__restrict__ out,
+                                                                  unsigned long long *err) {
+    gather_slots<K, P, kFromCache, false, false>(s, c, c.host_payload, ids, nullptr, nullptr, n_items, 1, 0, out, err);
+}
+
 // Per cluster: where its rows start, their distance, and the bit at which every 128-word
 // tile of a row starts. One wave per cluster.
 __global__ __launch_bounds__(kBlock) void k_group_info(DevStream s, GroupInfo *__restrict__ groups,
@@ -322,34 +357,48 @@ hipError_t launch_group_info(const DevStream &s, GroupInfo *groups, uint32_t *ti
     return hipGetLastError();
 }
 
-hipError_t launch_gather_slots(const DevStream &s, const uint8_t *payload, const int64_t *ids, const uint32_t *sg,
-                               const uint32_t *soff, uint64_t n, void *out, unsigned long long *err,
-                               hipStream_t stream) {
+hipError_t launch_gather_slots(const DevStream &s, const CacheView *cache, const uint8_t *payload, const int64_t *ids,
+                               const uint32_t *sg, const uint32_t *soff, uint64_t n, void *out,
+                               unsigned long long *err, hipStream_t stream) {
     auto *o = static_cast<uint32_t *>(out);
     const uint32_t tiles = s.W <= 256 ? 1u : (s.W + 255u) / 256u;
     const uint64_t items = n * tiles;
     const uint32_t per = (uint32_t)kWave / s.slot_pairs;
     const uint64_t waves = (items + per - 1) / per;
     const dim3 grid((unsigned)((waves + kWavesPerBlock - 1) / kWavesPerBlock)), block(kBlock);
-    auto go = [&](auto k, auto tiled) {
-        constexpr int K = decltype(k)::value;
-        constexpr bool T = decltype(tiled)::value;
+    auto go = [&](auto k, auto tiled, auto src, auto split) {
+        constexpr int K = decltype(k)::value, SRC = decltype(src)::value;
+        constexpr bool T = decltype(tiled)::value, SP = decltype(split)::value;
         auto pairs = [&](auto p) {
             constexpr int P = decltype(p)::value;
-            if (soff)
-                hipLaunchKernelGGL((k_gather_slots<K, P, true, T>), grid, block, 0, stream, s, payload, ids, sg, soff,
-                                   items, tiles, div_magic(tiles), o, err);
+            if constexpr (SRC == kFromCache)
+                hipLaunchKernelGGL((k_cache_gather_slots<K, P>), grid, block, 0, stream, s, *cache, ids, items, o, err);
             else
-                hipLaunchKernelGGL((k_gather_slots<K, P, false, T>), grid, block, 0, stream, s, payload, ids, sg, soff,
-                                   items, tiles, div_magic(tiles), o, err);
+                hipLaunchKernelGGL((k_gather_slots<K, P, SRC, T, SP>), grid, block, 0, stream, s, payload, ids, sg,
+                                   soff, items, tiles, div_magic(tiles), o, err);
         };
         if (s.slot_pairs == 8) pairs(std::integral_constant<int, 8>{});
         else pairs(std::integral_constant<int, 16>{});
     };
-    if (s.W <= 64) go(std::integral_constant<int, 1>{}, std::false_type{});
-    else if (s.W <= 128) go(std::integral_constant<int, 2>{}, std::false_type{});
-    else if (s.W <= 256) go(std::integral_constant<int, 4>{}, std::false_type{});
-    else go(std::integral_constant<int, 4>{}, std::true_type{});
+    // A window of device memory is read as separate dwords at one or two words per lane (4-5%
+    // faster than one load) and as one load at four (17% faster). From host memory always as
+    // one: its reads bypass the L2, so that every load of a line is a read over PCIe.
+    auto narrow = [&](auto k) {
+        if (cache) go(k, std::false_type{}, std::integral_constant<int, kFromCache>{}, std::false_type{});
+        else if (s.payload_host) go(k, std::false_type{}, std::integral_constant<int, kFromIds>{}, std::false_type{});
+        else if (soff) go(k, std::false_type{}, std::integral_constant<int, kFromStage>{}, std::true_type{});
+        else go(k, std::false_type{}, std::integral_constant<int, kFromIds>{}, std::true_type{});
+    };
+    auto wide = [&](auto tiled) {
+        constexpr std::integral_constant<int, 4> k{};
+        if (soff) go(k, tiled, std::integral_constant<int, kFromStage>{}, std::false_type{});
+        else go(k, tiled, std::integral_constant<int, kFromIds>{}, std::false_type{});
+    };
+    if (s.W <= 64) narrow(std::integral_constant<int, 1>{});
+    else if (s.W <= 128) narrow(std::integral_constant<int, 2>{});
+    else if (cache || s.payload_host) return hipErrorInvalidValue;   // (they have lane-order slots)
+    else if (s.W <= 256) wide(std::false_type{});
+    else wide(std::true_type{});
     return hipGetLastError();
 }
 

@@ -1169,7 +1169,7 @@ hipError_t launch_gather(const DevStream &s, const uint8_t *payload, const int64
                          const uint32_t *soff, uint64_t n, void *out, unsigned long long *err, hipStream_t stream) {
     if (n == 0) return hipSuccess;
     if (s.part_m) return launch_part(s, payload, 0, ids, sg, soff, 0, n, out, err, stream);
-    if (s.slots && s.word_order) return launch_gather_slots(s, payload, ids, sg, soff, n, out, err, stream);
+    if (s.slots && s.word_order) return launch_gather_slots(s, nullptr, payload, ids, sg, soff, n, out, err, stream);
     const auto *p = reinterpret_cast<const uint32_t *>(payload);
     auto *o = static_cast<uint32_t *>(out);
     const int k = words_per_lane(s.W);
@@ -1203,8 +1203,12 @@ hipError_t launch_gather(const DevStream &s, const uint8_t *payload, const int64
         if (soff) {   // (a stage is device memory: with slots the gather above took it)
             hipLaunchKernelGGL((k_gather_rows<KK, R, true, kMetaRaw>), grid, block, 0, stream, s, p, ids, sg, soff, n, o, seg, err);
         } else {
-            if (s.slots) hipLaunchKernelGGL((k_gather_rows<KK, R, false, kMetaSlots>), grid, block, 0, stream, s, p, ids, sg, soff, n, o, seg, err);
-            else hipLaunchKernelGGL((k_gather_rows<KK, R, false, kMetaRaw>), grid, block, 0, stream, s, p, ids, sg, soff, n, o, seg, err);
+            if (s.slots) {   // (lane order: rows of more than 128 words, in place in host memory)
+                if constexpr (KK >= 4)
+                    hipLaunchKernelGGL((k_gather_rows<KK, R, false, kMetaSlots>), grid, block, 0, stream, s, p, ids, sg, soff, n, o, seg, err);
+            } else {
+                hipLaunchKernelGGL((k_gather_rows<KK, R, false, kMetaRaw>), grid, block, 0, stream, s, p, ids, sg, soff, n, o, seg, err);
+            }
         }
     };
 #define IBP_GATHER_ROWS(KK, RB) go(std::integral_constant<int, KK>{}, std::integral_constant<int, RB>{})

@@ -765,8 +765,10 @@ ibp_status open_impl(const void *stream, uint64_t stream_bytes, int device, uint
         return bail(fail(IBP_EHIP, "index upload failed"));
     const uint32_t W = d.row_bytes / 4;
     // gathers from device memory (payload or stage) read word-order slots, of rows of any
-    // size; those that read host memory in place lane-order ones
-    const bool word_order = flags == IBP_OPEN_PAYLOAD_DEVICE || flags == IBP_OPEN_PAYLOAD_HOST;
+    // size; those that read host memory in place as well for rows of at most 128 words, which
+    // a wave reads with one load, and else lane-order ones, where a load covers a stretch of
+    // the row's lines of its own
+    const bool word_order = flags == IBP_OPEN_PAYLOAD_DEVICE || flags == IBP_OPEN_PAYLOAD_HOST || W <= 128;
     if (d.flags == 0 && (W <= 512 || word_order)) {
         // the row gathers read a cluster's metadata for every row they decode: when every
         // cluster fits one, give each a compact slot as well

@@ -46,8 +46,8 @@ __device__ __forceinline__ uint64_t wave_slot() {
            (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
 }
 
-// How the row gathers read a cluster's Mask/Bitval words: the raw words, or the
-// cluster's compact slot (P = 8 or 16 {Mask, Bitval} u32 pairs, then the 4-bit pair
+// How the row-at-a-time gathers read a cluster's Mask/Bitval words: the raw words, or (rows of
+// 129 to 512 words in place in host memory) the cluster's compact slot in lane order (P = 8 or 16 {Mask, Bitval} u32 pairs, then the 4-bit pair
 // indices, lane l's K indices in bits [4Kl, 4Kl + 4K)), used when every cluster of the
 // stream fits one.
 enum { kMetaRaw = 0, kMetaSlots = 1 };
@@ -70,9 +70,7 @@ __device__ __forceinline__ void load_row_meta(RowMeta<K, FORM> &r, const uint32_
         r.v[0] = p.x;
         r.v[1] = p.y;
         const uint8_t *__restrict__ idx = slot + 8 * P;
-        if constexpr (K == 1) r.v[2] = idx[l >> 1];
-        else if constexpr (K == 2) r.v[2] = idx[l];
-        else if constexpr (K == 4) r.v[2] = reinterpret_cast<const uint16_t *>(idx)[l];
+        if constexpr (K == 4) r.v[2] = reinterpret_cast<const uint16_t *>(idx)[l];
         else r.v[2] = reinterpret_cast<const uint32_t *>(idx)[l];
     } else {
 #pragma unroll
@@ -99,10 +97,9 @@ __device__ __forceinline__ void hold_row_meta(RowMeta<K, FORM> &r) {
 template <int K, int FORM>
 __device__ __forceinline__ void expand_row_meta(const RowMeta<K, FORM> &r, uint32_t (&m)[K], uint32_t (&b)[K]) {
     if constexpr (FORM == kMetaSlots) {
-        const uint32_t bits = K == 1 ? r.v[2] >> ((lane_id() & 1u) * 4u) : r.v[2];
 #pragma unroll
         for (int j = 0; j < K; ++j) {
-            const int a = (int)(((bits >> (4 * j)) & 15u) * 4u);
+            const int a = (int)(((r.v[2] >> (4 * j)) & 15u) * 4u);
             m[j] = (uint32_t)__builtin_amdgcn_ds_bpermute(a, (int)r.v[0]);
             b[j] = (uint32_t)__builtin_amdgcn_ds_bpermute(a, (int)r.v[1]);
         }

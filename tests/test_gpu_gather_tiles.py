@@ -1,5 +1,5 @@
 """GPU parity of the gathers that read word-order metadata slots (payload or stage in device
-memory), at the sizes where their tiling can go wrong: one, two and four words per lane and
+memory, or rows of at most 128 words in place in host memory), at the sizes where their tiling can go wrong: one, two and four words per lane and
 rows of several 256-word tiles, one word to either side of each boundary; slots of 8 and 16
 pairs (8 and 4 items per wave); words of one, two, three, four and more runs of variant bits,
 mixed within one wave; batches that end inside a wave; ids outside the table. Expected rows
@@ -131,3 +131,42 @@ def test_host_ids_in_place_and_copied(torch):
         torch.cuda.synchronize()
         for ids, out in calls:
             assert np.array_equal(out.cpu().numpy().reshape(-1, L), rows[ids]), ids.size
+
+
+@pytest.mark.parametrize("placement", ["zero_copy", "zero_copy_aligned", "cache"])
+@pytest.mark.parametrize("kind", sorted(KINDS))
+@pytest.mark.parametrize("W", [1, 2, 31, 63, 64, 65, 127, 128, 129, 200])
+def test_host_memory_in_place(torch, W, kind, placement):
+    """The same gather with the packed rows in pinned host memory (rows of at most 128 words;
+    wider ones take the row-at-a-time kernel), and behind the row cache: hits, misses and ids
+    outside the table mixed within a wave, and counted."""
+    G = 40
+    n, L = G * len(KINDS[kind]) * 2 + 3, 4 * W
+    rows = rows_of_runs(W, n, G, KINDS[kind], seed=W + 1)
+    rng = np.random.default_rng(W)
+    flags = (ibp.IBP_OPEN_PAYLOAD_HOST_ZERO_COPY_ALIGNED if placement == "zero_copy_aligned"
+             else ibp.IBP_OPEN_PAYLOAD_HOST_ZERO_COPY)
+    with ibp.ibp_open(oracle.compress(rows, G), 0, flags) as h:
+        held = rng.permutation(n)[:n // 3]
+        cache = ibp.ibp_cache_create(h, held) if placement == "cache" else None
+        for count in (1, 8, 9, 2 * n + 1):
+            ids = rng.integers(0, n, size=count).astype(np.int64)
+            bad = rng.random(count) < 0.1
+            sent = torch.from_numpy(np.where(bad, np.where(ids % 2, -1 - ids, n + ids), ids)).cuda()
+            out = torch.full((count * L + 64,), 0xA5, dtype=torch.uint8, device="cuda")
+            if cache is not None:
+                ibp.ibp_cache_reset_stats(cache)
+                ibp.ibp_cache_gather(cache, sent, out, out_cap=count * L)
+                st = ibp.ibp_cache_get_stats(cache)
+                hits = int(np.isin(ids[~bad], held).sum())
+                assert (st["hits"], st["misses"]) == (hits, int((~bad).sum()) - hits)
+            else:
+                ibp.ibp_gather_decompress_device(h, sent, out, out_cap=count * L)
+            torch.cuda.synchronize()
+            want = rows[ids].copy()
+            want[bad] = 0
+            assert np.array_equal(out[:count * L].cpu().numpy().reshape(count, L), want), count
+            assert (out[count * L:].cpu().numpy() == 0xA5).all(), "wrote past the output"
+            assert ibp.ibp_device_errors(h) == bad.sum()
+        if cache is not None:
+            ibp.ibp_cache_destroy(cache)
