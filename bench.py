@@ -66,7 +66,8 @@ HBM_PEAK_GBS = 8000.0
 # value recorded with them)
 KERNEL_SOURCES = [os.path.join(ROOT, "paper_2605_30728_amd", "csrc", f)
                   for f in ("ibp_kernels.hip", "ibp_gather_kernels.hip", "ibp_part_kernels.hip", "ibp_cache_kernels.hip",
-                            "ibp_wave.hpp", "ibp_tile.hpp", "ibp_cache.hpp", "ibp_device.hpp", "ibp_runtime.hip", "ibp_meta_slots.cpp")]
+                            "ibp_wave.hpp", "ibp_tile.hpp", "ibp_cache.hpp", "ibp_device.hpp", "ibp_runtime.hip",
+                            "ibp_meta_slots.cpp")]
 
 
 def code_sha256(texts):
@@ -117,12 +118,14 @@ def kernel_name(workload, W, part=False):
     if part:
         maxr = {1: 4, 2: 4, 4: 2, 8: 1}[k]
         src = 'ids' if workload in GATHERS else 'range'
+        if W <= 128:
+            return f"k_part_narrow<{k},{maxr},{src}>"
         if W <= 512:
             return f"k_part_batched<{k},{maxr},{ {1: 8, 2: 4, 4: 2, 8: 1}[k] },{src}>"
         return f"k_part_rows<{k},{maxr},{src}>"
     if workload in GATHERS:
         return f"k_gather_slots<{min(k, 4)}>"   # every workload's clusters have metadata slots
-    return f"k_decompress<{k},{ {1: 4, 2: 4, 4: 2, 8: 1}[k] },true>"   # device payload: split window loads
+    return f"k_decompress<{min(k, 2)},4,true>"   # device payload: split window loads, tiles of wide rows
 
 
 def measured_traffic(workload, part=False):
