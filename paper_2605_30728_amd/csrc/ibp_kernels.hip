@@ -1136,6 +1136,13 @@ hipError_t launch_decompress(const DevStream &s, const uint8_t *payload, uint64_
     const uint32_t upg = (s.G + rpu - 1) / rpu;
     const uint64_t n_units = (g1 - g0 + 1) * upg;
     const uint64_t blocks = (n_units * tiles + kWavesPerBlock - 1) / kWavesPerBlock;
+    if (blocks > kMaxBlocks && n > 1) {
+        const uint64_t h = n / 2;
+        const hipError_t e = launch_decompress(s, payload, pay_base, out, first, h, stream);
+        return e != hipSuccess ? e
+                               : launch_decompress(s, payload, pay_base, static_cast<uint32_t *>(out) + h * s.W,
+                                                   first + h, n - h, stream);
+    }
     const auto *p = reinterpret_cast<const uint32_t *>(payload);
     auto *o = static_cast<uint32_t *>(out);
     dim3 grid((unsigned)blocks), block(kBlock);

@@ -15,6 +15,10 @@ inline constexpr int kWave = 64;
 inline constexpr int kWavesPerBlock = 4;
 inline constexpr int kBlock = kWave * kWavesPerBlock;
 
+// Blocks of one launch: a grid's threads are counted in 32 bits, and one of 2^32 or more runs
+// short without an error. A launcher whose waves take few rows halves a call that has more.
+inline constexpr uint64_t kMaxBlocks = 0xFFFFFFFFull / kBlock;
+
 __device__ __forceinline__ uint32_t lane_id() { return __lane_id(); }
 
 // Inclusive prefix sum over the 64 lanes of a wave: row_shr 1/2/4/8 scan each row of
@@ -47,9 +51,9 @@ __device__ __forceinline__ uint64_t wave_slot() {
 }
 
 // How the row-at-a-time gathers read a cluster's Mask/Bitval words: the raw words, or (rows of
-// 129 to 512 words in place in host memory) the cluster's compact slot in lane order (P = 8 or 16 {Mask, Bitval} u32 pairs, then the 4-bit pair
-// indices, lane l's K indices in bits [4Kl, 4Kl + 4K)), used when every cluster of the
-// stream fits one.
+// 129 to 512 words in place in host memory) the cluster's compact slot in lane order (P = 8
+// or 16 {Mask, Bitval} u32 pairs, then the 4-bit pair indices, lane l's K indices in bits
+// [4Kl, 4Kl + 4K)), used when every cluster of the stream fits one.
 enum { kMetaRaw = 0, kMetaSlots = 1 };
 
 // A row's metadata as loaded: raw v[2j] = Mask, v[2j+1] = Bitval of word l + 64j; slots

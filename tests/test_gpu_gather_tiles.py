@@ -170,3 +170,51 @@ def test_host_memory_in_place(torch, W, kind, placement):
             assert ibp.ibp_device_errors(h) == bad.sum()
         if cache is not None:
             ibp.ibp_cache_destroy(cache)
+
+
+@pytest.mark.parametrize("W", [20, 100, 200, 600])
+def test_output_at_any_byte(torch, W):
+    """An output that starts off a word boundary (a view into a larger buffer): every kernel
+    that stores through a descriptor over its output row, and not a byte beside the output."""
+    G = 40
+    n, L = G * 6 + 3, 4 * W
+    rows = rows_of_runs(W, n, G, KINDS["any"], seed=W + 2)
+    ids = np.random.default_rng(W).integers(0, n, size=301).astype(np.int64)
+    d_ids = torch.from_numpy(ids).cuda()
+    clustered, one_mask = oracle.compress(rows, G), oracle.compress(rows, n, chunk_bytes=4, threshold=(4, 5))
+
+    def check(call, want):
+        for at in (1, 2, 3):
+            buf = torch.full((want.size + 256,), 0xA5, dtype=torch.uint8, device="cuda")
+            call(buf[64 + at:64 + at + want.size])
+            torch.cuda.synchronize()
+            got = buf.cpu().numpy()
+            assert np.array_equal(got[64 + at:64 + at + want.size], want.reshape(-1)), at
+            assert (got[:64 + at] == 0xA5).all() and (got[64 + at + want.size:] == 0xA5).all(), at
+
+    for stream in (clustered, one_mask):
+        for flags in (ibp.IBP_OPEN_PAYLOAD_DEVICE, ibp.IBP_OPEN_PAYLOAD_HOST, ibp.IBP_OPEN_PAYLOAD_HOST_ZERO_COPY):
+            with ibp.ibp_open(stream, 0, flags) as h:
+                check(lambda o: ibp.ibp_decompress(h, 3, n - 3, o), rows[3:])
+                check(lambda o: ibp.ibp_gather_decompress(h, ids, o), rows[ids])
+    if W <= 512:
+        with ibp.ibp_open(clustered, 0, ibp.IBP_OPEN_PAYLOAD_HOST_ZERO_COPY) as h:
+            cache = ibp.ibp_cache_create(h, np.arange(0, n, 3))
+            check(lambda o: ibp.ibp_cache_gather(cache, d_ids, o), rows[ids])
+            ibp.ibp_cache_destroy(cache)
+
+
+def test_more_rows_than_one_launch(torch):
+    """At 8 rows per wave, 2^29 rows are 2^32 threads, one more than a launch may have."""
+    n, G, count = 4000, 32, (1 << 29) + 5
+    if torch.cuda.mem_get_info()[0] < 16 << 30:
+        pytest.skip("needs 16 GB of device memory")
+    rows = rows_of_runs(1, n, G, KINDS["two"], seed=6)
+    table = torch.from_numpy(rows.view(np.int32).reshape(-1).copy()).cuda()
+    with ibp.ibp_open(oracle.compress(rows, G), 0) as h:
+        ids = torch.randint(0, n, (count,), device="cuda")
+        out = torch.zeros(count, dtype=torch.int32, device="cuda")
+        ibp.ibp_gather_decompress_device(h, ids, out)
+        torch.cuda.synchronize()
+        for lo in range(0, count, 1 << 27):
+            assert torch.equal(out[lo:lo + (1 << 27)], table[ids[lo:lo + (1 << 27)]]), lo
