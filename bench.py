@@ -66,8 +66,8 @@ HBM_PEAK_GBS = 8000.0
 # value recorded with them)
 KERNEL_SOURCES = [os.path.join(ROOT, "paper_2605_30728_amd", "csrc", f)
                   for f in ("ibp_kernels.hip", "ibp_gather_kernels.hip", "ibp_part_kernels.hip", "ibp_cache_kernels.hip",
-                            "ibp_wave.hpp", "ibp_tile.hpp", "ibp_cache.hpp", "ibp_device.hpp", "ibp_runtime.hip",
-                            "ibp_meta_slots.cpp")]
+                            "ibp_wave.hpp", "ibp_tile.hpp", "ibp_cache.hpp", "ibp_device.hpp", "ibp_grid.hpp",
+                            "ibp_runtime.hip", "ibp_meta_slots.cpp")]
 
 
 def code_sha256(texts):

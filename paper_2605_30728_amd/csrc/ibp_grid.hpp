@@ -1,0 +1,78 @@
+// How a call's rows are shared out over the waves of a launch: plain arithmetic that the
+// launchers and the kernels share and that also compiles without HIP.
+#pragma once
+
+#include <algorithm>
+#include <cstdint>
+
+#ifdef __HIPCC__
+#define IBP_HD __host__ __device__ __forceinline__
+#else
+#define IBP_HD inline
+#endif
+
+namespace ibp {
+namespace dev {
+
+inline constexpr int kWave = 64;
+inline constexpr int kWavesPerBlock = 4;
+inline constexpr int kBlock = kWave * kWavesPerBlock;
+
+// Blocks of one launch: a grid's threads are counted in 32 bits, and one of 2^32 or more runs
+// short without an error. A launcher whose waves take few rows halves a call that has more.
+inline constexpr uint64_t kMaxBlocks = 0xFFFFFFFFull / kBlock;
+
+inline uint64_t blocks_of_waves(uint64_t waves) { return (waves + kWavesPerBlock - 1) / kWavesPerBlock; }
+
+// The slices (at most `rows` rows of one cluster each) that hold rows [first, first + n): only
+// those, whatever the clusters' nominal size, so that n bounds their number.
+struct RowSlices {
+    uint64_t g0;          // first cluster
+    uint32_t rows;        // rows per slice
+    uint32_t per_group;   // slices of a whole cluster
+    uint32_t skip;        // slices of the first cluster before the range
+    uint64_t count;
+};
+
+// n >= 1, G >= 1, rows >= 1.
+inline RowSlices row_slices(uint64_t first, uint64_t n, uint32_t G, uint32_t rows) {
+    RowSlices u;
+    const uint64_t last = first + n - 1, g1 = last / G;
+    u.g0 = first / G;
+    u.rows = rows;
+    u.per_group = (G - 1) / rows + 1;
+    u.skip = (uint32_t)((first - u.g0 * G) / rows);
+    u.count = (g1 - u.g0) * u.per_group + (last - g1 * G) / rows - u.skip + 1;
+    return u;
+}
+
+// Cluster and slice of unit i (below count, and below 2^32: one launch has fewer waves).
+IBP_HD void slice_of(const RowSlices &u, uint32_t i, uint64_t &group, uint32_t &slice) {
+    const uint32_t head = u.per_group - u.skip;
+    if (i < head) {
+        group = u.g0;
+        slice = u.skip + i;
+    } else {
+        const uint32_t q = (i - head) / u.per_group;
+        group = u.g0 + 1 + q;
+        slice = i - head - q * u.per_group;
+    }
+}
+
+// The slices of a contiguous decompress, each decoded by `tiles` waves of K words per lane: a
+// whole cluster (at most 64 rows), halved in whole batches while the launch would have fewer
+// than 16k waves (2 per wave slot of the chip; 128k at one word per lane), down to one batch
+// of rows; every slice repeats its cluster's setup, which is small next to its rows. Measured:
+// 524,288 rows of 64 words 42.4 us with 32 rows per wave (16k waves), 40.5 with 8; 2,097,152
+// rows 160.5 and 154; 50k rows of 600 words in tiles 45.4 us at 16k waves and 47.9 at 32k.
+inline RowSlices decompress_slices(uint64_t first, uint64_t n, uint32_t G, int K, uint32_t tiles) {
+    const uint32_t min_rows = K == 1 ? 8 : (K == 2 ? 4 : (K == 4 ? 2 : 1));
+    const uint64_t enough = K == 1 ? 131072 : 16384;
+    uint32_t rows = std::min<uint32_t>(G, 64);
+    while (rows > min_rows && row_slices(first, n, G, rows).count * tiles < enough)
+        rows = ((rows + 1) / 2 + min_rows - 1) / min_rows * min_rows;
+    return row_slices(first, n, G, rows);
+}
+
+}  // namespace dev
+}  // namespace ibp

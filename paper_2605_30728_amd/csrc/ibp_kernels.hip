@@ -170,30 +170,28 @@ __device__ __forceinline__ void decode_rows_tiled(const uint32_t *__restrict__ m
 }
 
 
-// One wave per unit = (cluster, slice of at most rpu rows of it) or, TILED, (cluster, slice,
+// One wave per unit = a slice of a cluster's rows (decompress_slices) or, TILED, (slice,
 // tile of 64K words): the cluster's tile table gives the bit at which the tile starts, so
 // the tiles of wide rows are as independent as narrow rows.
 template <int K, int MAXR, bool SPLIT, bool TILED>
 __global__ __launch_bounds__(kBlock) void k_decompress(DevStream s, const uint32_t *__restrict__ pay32,
                                                         uint64_t pay_base, uint32_t *__restrict__ out,
-                                                        uint64_t first, uint64_t n, uint64_t g0,
-                                                        uint64_t n_units, uint32_t upg, uint32_t rpu) {
-    uint64_t unit;
-    uint32_t w0 = 0;
+                                                        uint64_t first, uint64_t n, RowSlices units) {
+    uint32_t unit = (uint32_t)wave_slot(), w0 = 0;
     if constexpr (TILED) {
         // the tiles of a slice side by side on one XCD: neighbours share a line of every row
-        const uint64_t slot = (uint64_t)xcd_block(blockIdx.x, gridDim.x) * kWavesPerBlock +
+        const uint32_t slot = xcd_block(blockIdx.x, gridDim.x) * kWavesPerBlock +
                               (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
         unit = slot / s.tiles128;
-        w0 = (uint32_t)(slot - unit * s.tiles128) * (kWave * K);
-    } else {
-        unit = wave_slot();
+        w0 = (slot - unit * s.tiles128) * (kWave * K);
     }
-    if (unit >= n_units) return;
-    const uint64_t g = g0 + unit / upg;
+    if (unit >= units.count) return;
+    uint64_t g;
+    uint32_t slice;
+    slice_of(units, unit, g, slice);
     const uint64_t gstart = g * s.G;
-    uint64_t r_lo = gstart + (unit % upg) * (uint64_t)rpu;
-    uint64_t r_hi = min(r_lo + rpu, min(gstart + s.G, s.n_rows));
+    uint64_t r_lo = gstart + (uint64_t)slice * units.rows;
+    uint64_t r_hi = min(r_lo + units.rows, min(gstart + s.G, s.n_rows));
     r_lo = max(r_lo, first);
     r_hi = min(r_hi, first + n);
     if (r_lo >= r_hi) return;
@@ -1114,13 +1112,6 @@ hipError_t launch_decompress(const DevStream &s, const uint8_t *payload, uint64_
                              uint64_t first, uint64_t n, hipStream_t stream) {
     if (n == 0) return hipSuccess;
     if (s.part_m) return launch_part(s, payload, pay_base, nullptr, nullptr, nullptr, first, n, out, nullptr, stream);
-    const uint64_t g0 = first / s.G, g1 = (first + n - 1) / s.G;
-    // rows per wave: a whole cluster (at most 64 rows), halved in whole batches while the
-    // launch would have fewer than 16k waves (2 per wave slot of the chip; 128k at one word
-    // per lane), down to one batch of rows; every slice repeats its cluster's setup, which is
-    // small next to its rows. Measured: 524,288 rows of 64 words 42.4 us with 32 rows per wave
-    // (16k waves), 40.5 with 8; 2,097,152 rows 160.5 and 154; 50k rows of 600 words in tiles
-    // 45.4 us at 16k waves and 47.9 at 32k
     // Rows of more than 128 words in device memory: 128-word tiles, each a unit of its own
     // (a wave that walks a wide row's tiles has one or two rows' loads in flight and rebuilds
     // runs in a loop: 50k rows of 600 words of bf16 pairs 117 us, in tiles 45; 50k of 300
@@ -1128,14 +1119,8 @@ hipError_t launch_decompress(const DevStream &s, const uint8_t *payload, uint64_
     const bool tiled = s.tile_bits && !s.payload_host;
     const uint32_t tiles = tiled ? s.tiles128 : 1;
     const int k = tiled ? 2 : words_per_lane(s.W);
-    const uint32_t min_rows = k == 1 ? 8 : (k == 2 ? 4 : (k == 4 ? 2 : 1));
-    uint32_t rpu = s.G <= 64 ? s.G : 64;
-    const uint64_t enough = k == 1 ? 131072 : 16384;
-    while (rpu > min_rows && (g1 - g0 + 1) * ((s.G + rpu - 1) / rpu) * tiles < enough)
-        rpu = ((rpu + 1) / 2 + min_rows - 1) / min_rows * min_rows;
-    const uint32_t upg = (s.G + rpu - 1) / rpu;
-    const uint64_t n_units = (g1 - g0 + 1) * upg;
-    const uint64_t blocks = (n_units * tiles + kWavesPerBlock - 1) / kWavesPerBlock;
+    const RowSlices units = decompress_slices(first, n, s.G, k, tiles);
+    const uint64_t blocks = blocks_of_waves(units.count * tiles);
     if (blocks > kMaxBlocks && n > 1) {
         const uint64_t h = n / 2;
         const hipError_t e = launch_decompress(s, payload, pay_base, out, first, h, stream);
@@ -1149,8 +1134,7 @@ hipError_t launch_decompress(const DevStream &s, const uint8_t *payload, uint64_
     auto go = [&](auto kk, auto mr, auto split, auto tile) {
         constexpr int KK = decltype(kk)::value, MR = decltype(mr)::value;
         constexpr bool SP = decltype(split)::value, TI = decltype(tile)::value;
-        hipLaunchKernelGGL((k_decompress<KK, MR, SP, TI>), grid, block, 0, stream, s, p, pay_base, o, first, n, g0,
-                           n_units, upg, rpu);
+        hipLaunchKernelGGL((k_decompress<KK, MR, SP, TI>), grid, block, 0, stream, s, p, pay_base, o, first, n, units);
     };
     // two dword loads per window from device memory, one 8-byte load from pinned host memory
     // (where a wave also takes whole rows: a tile's first and last lines would cross PCIe

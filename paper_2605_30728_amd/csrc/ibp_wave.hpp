@@ -7,17 +7,10 @@
 #include <hip/hip_runtime.h>
 
 #include "ibp_device.hpp"
+#include "ibp_grid.hpp"
 
 namespace ibp {
 namespace dev {
-
-inline constexpr int kWave = 64;
-inline constexpr int kWavesPerBlock = 4;
-inline constexpr int kBlock = kWave * kWavesPerBlock;
-
-// Blocks of one launch: a grid's threads are counted in 32 bits, and one of 2^32 or more runs
-// short without an error. A launcher whose waves take few rows halves a call that has more.
-inline constexpr uint64_t kMaxBlocks = 0xFFFFFFFFull / kBlock;
 
 __device__ __forceinline__ uint32_t lane_id() { return __lane_id(); }
 

@@ -57,3 +57,16 @@ def test_many_batches_per_wave(torch, W, n, G):
     with ibp.ibp_open(ibp.ibp_compress(rows, G), 0) as h:
         check(torch, h, rows, 0, n)
         check(torch, h, rows, 17, n - 40)
+
+
+@pytest.mark.parametrize("placement", sorted(FLAGS))
+@pytest.mark.parametrize("W", [20, 100, 256, 1000, 2048])
+@pytest.mark.parametrize("G", [1 << 29, 1 << 31, (1 << 32) - 1])
+def test_one_mask_for_everything(torch, W, G, placement):
+    """A nominal cluster far larger than the table (one Mask for all rows): a launch's blocks
+    follow from the rows of the range."""
+    n = 300
+    rows = structured_rows("floats", n, 4 * W, seed=W)
+    with ibp.ibp_open(ibp.ibp_compress(rows, G), 0, FLAGS[placement]) as h:
+        for first, count in ((0, n), (7, 200), (n - 1, 1)):
+            check(torch, h, rows, first, count)
