@@ -331,29 +331,30 @@ __global__ __launch_bounds__(kBlock, 8) void k_cache_gather_slots(DevStream s, C
 }
 
 // Per cluster: where its rows start, their distance, and the bit at which every 128-word
-// tile of a row starts. One wave per cluster.
+// tile of a row starts. A wave per cluster, the clusters in strides of the grid.
 __global__ __launch_bounds__(kBlock) void k_group_info(DevStream s, GroupInfo *__restrict__ groups,
                                                        uint32_t *__restrict__ tile_bits) {
-    const uint64_t g = wave_slot();
-    if (g >= s.n_groups) return;
     const uint32_t l = lane_id(), W = s.W;
-    const uint32_t *__restrict__ mg = s.meta + g * 2ull * W;
-    uint32_t bits = 0;
-    for (uint32_t w0 = 0, t = 0; w0 < W; w0 += 128, ++t) {
-        if (tile_bits && l == 0) tile_bits[g * s.tiles128 + t] = bits;
-        uint32_t n = 0;
-        for (uint32_t w = w0 + l; w < min(W, w0 + 128u); w += kWave) n += (uint32_t)__builtin_popcount(~mg[w]);
-        bits += wave_sum(n);
+    for (uint64_t g = wave_slot(); g < s.n_groups; g += (uint64_t)gridDim.x * kWavesPerBlock) {
+        const uint32_t *__restrict__ mg = s.meta + g * 2ull * W;
+        uint32_t bits = 0;
+        for (uint32_t w0 = 0, t = 0; w0 < W; w0 += 128, ++t) {
+            if (tile_bits && l == 0) tile_bits[g * s.tiles128 + t] = bits;
+            uint32_t n = 0;
+            for (uint32_t w = w0 + l; w < min(W, w0 + 128u); w += kWave) n += (uint32_t)__builtin_popcount(~mg[w]);
+            bits += wave_sum(n);
+        }
+        if (groups && l == 0)
+            groups[g] = GroupInfo{s.index[g], (uint32_t)row_stride((bits + 7u) >> 3, s.row_align), bits};
     }
-    if (groups && l == 0) groups[g] = GroupInfo{s.index[g], (uint32_t)row_stride((bits + 7u) >> 3, s.row_align), bits};
 }
 
 }  // namespace
 
 hipError_t launch_group_info(const DevStream &s, GroupInfo *groups, uint32_t *tile_bits, hipStream_t stream) {
     if (s.n_groups == 0) return hipSuccess;
-    const uint64_t blocks = (s.n_groups + kWavesPerBlock - 1) / kWavesPerBlock;
-    hipLaunchKernelGGL(k_group_info, dim3((unsigned)blocks), dim3(kBlock), 0, stream, s, groups, tile_bits);
+    hipLaunchKernelGGL(k_group_info, dim3((unsigned)cluster_blocks(s.n_groups)), dim3(kBlock), 0, stream, s, groups,
+                       tile_bits);
     return hipGetLastError();
 }
 

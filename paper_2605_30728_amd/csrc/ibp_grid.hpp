@@ -74,5 +74,11 @@ inline RowSlices decompress_slices(uint64_t first, uint64_t n, uint32_t G, int K
     return row_slices(first, n, G, rows);
 }
 
+// The waves of a kernel that takes a stream's clusters in strides of the grid: one per cluster,
+// up to what fills the chip many times over.
+inline uint64_t cluster_blocks(uint64_t n_groups) {
+    return std::min<uint64_t>(blocks_of_waves(n_groups), 1u << 18);
+}
+
 }  // namespace dev
 }  // namespace ibp

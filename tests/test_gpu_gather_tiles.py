@@ -218,3 +218,18 @@ def test_more_rows_than_one_launch(torch):
         torch.cuda.synchronize()
         for lo in range(0, count, 1 << 27):
             assert torch.equal(out[lo:lo + (1 << 27)], table[ids[lo:lo + (1 << 27)]]), lo
+
+
+def test_more_clusters_than_one_launch(torch):
+    """At a wave per cluster, 2^26 clusters are 2^32 threads: the clusters' places in the
+    payload have to be there for the last ones too."""
+    n = (1 << 27) + 9
+    if torch.cuda.mem_get_info()[0] < 32 << 30:
+        pytest.skip("needs 32 GB of device memory")
+    rows = np.random.default_rng(7).integers(0, 1 << 32, size=n, dtype=np.uint32)
+    ids = np.concatenate([np.random.default_rng(8).integers(0, n, size=4000), np.arange(n - 900, n)]).astype(np.int64)
+    with ibp.ibp_open(ibp.ibp_compress(rows.view(np.uint8).reshape(n, 4), 2), 0) as h:
+        out = torch.empty(ids.size, dtype=torch.int32, device="cuda")
+        ibp.ibp_gather_decompress_device(h, torch.from_numpy(ids).cuda(), out)
+        torch.cuda.synchronize()
+        assert np.array_equal(out.cpu().numpy().view(np.uint32), rows[ids])

@@ -19,6 +19,7 @@ uint64_t max_blocks() { return kMaxBlocks; }
 uint64_t decompress_blocks(uint64_t first, uint64_t n, uint32_t G, int K, uint32_t tiles) {
     return blocks_of_waves(decompress_slices(first, n, G, K, tiles).count * tiles);
 }
+uint64_t cluster_grid(uint64_t n_groups) { return cluster_blocks(n_groups); }
 uint64_t slices(uint64_t first, uint64_t n, uint32_t G, uint32_t rows) { return row_slices(first, n, G, rows).count; }
 uint64_t decompress_rows(uint64_t first, uint64_t n, uint32_t G, int K, uint32_t tiles) {
     return decompress_slices(first, n, G, K, tiles).rows;
@@ -42,7 +43,7 @@ def grid(tmp_path_factory):
     subprocess.run(["g++", "-O1", "-std=c++17", "-shared", "-fPIC", f"-I{CSRC}", str(d / "shim.cpp"), "-o", so], check=True)
     lib = ctypes.CDLL(so)
     u64, u32, i32 = ctypes.c_uint64, ctypes.c_uint32, ctypes.c_int
-    for name, args in {"max_blocks": [], "decompress_blocks": [u64, u64, u32, i32, u32], "slices": [u64, u64, u32, u32],
+    for name, args in {"max_blocks": [], "cluster_grid": [u64], "decompress_blocks": [u64, u64, u32, i32, u32], "slices": [u64, u64, u32, u32],
                        "decompress_rows": [u64, u64, u32, i32, u32], "unit_row": [u64, u64, u32, u32, u32]}.items():
         getattr(lib, name).argtypes = args
         getattr(lib, name).restype = u64
@@ -79,3 +80,8 @@ def test_decompress_blocks_follow_the_rows(grid, W, G):
     while grid.decompress_blocks(3, n, G, K, tiles) > grid.max_blocks():
         n //= 2
     assert n >= 1 << 20
+
+
+@pytest.mark.parametrize("n", [1, 4, 5, 1 << 20, (1 << 26) - 1, 1 << 26, (1 << 26) + 1, 1 << 33])
+def test_cluster_grid_is_bounded(grid, n):
+    assert 1 <= grid.cluster_grid(n) <= min((n + 3) // 4, grid.max_blocks())
