@@ -127,12 +127,18 @@ hipError_t launch_cache_gather(const DevStream &s, const CacheView &c, const int
     if (s.slots && s.word_order)
         return launch_gather_slots(s, &c, c.host_payload, ids, nullptr, nullptr, n, out, err, stream);
     auto *o = static_cast<uint32_t *>(out);
-    auto grid = [&](uint64_t rb) { return dim3((unsigned)(((n + rb - 1) / rb + kWavesPerBlock - 1) / kWavesPerBlock)); };
+    const uint32_t rb_sel = s.W <= 64 ? 8 : (s.W <= 128 ? 4 : (s.W <= 256 ? 2 : 1));
+    const uint64_t blocks = blocks_of_waves((n + rb_sel - 1) / rb_sel);
+    if (too_many_blocks(blocks, n))
+        return in_halves(n, [&](uint64_t i, uint64_t count) {
+            return launch_cache_gather(s, c, ids + i, count, o + i * s.W, err, stream);
+        });
+    const dim3 grid((unsigned)blocks);
     auto go = [&](auto kk, auto rb) {
         constexpr int KK = decltype(kk)::value, R = decltype(rb)::value;
         if (s.slots) {   // (lane order: rows of more than 128 words)
-            if constexpr (KK >= 4) hipLaunchKernelGGL((k_cache_gather<KK, R, kMetaSlots>), grid(R), dim3(kBlock), 0, stream, s, c, ids, n, o, err);
-        } else hipLaunchKernelGGL((k_cache_gather<KK, R, kMetaRaw>), grid(R), dim3(kBlock), 0, stream, s, c, ids, n, o, err);
+            if constexpr (KK >= 4) hipLaunchKernelGGL((k_cache_gather<KK, R, kMetaSlots>), grid, dim3(kBlock), 0, stream, s, c, ids, n, o, err);
+        } else hipLaunchKernelGGL((k_cache_gather<KK, R, kMetaRaw>), grid, dim3(kBlock), 0, stream, s, c, ids, n, o, err);
     };
     if (s.W <= 64) go(std::integral_constant<int, 1>{}, std::integral_constant<int, 8>{});
     else if (s.W <= 128) go(std::integral_constant<int, 2>{}, std::integral_constant<int, 4>{});

@@ -366,15 +366,12 @@ hipError_t launch_gather_slots(const DevStream &s, const CacheView *cache, const
     const uint64_t items = n * tiles;
     const uint32_t per = (uint32_t)kWave / s.slot_pairs;
     const uint64_t waves = (items + per - 1) / per;
-    const uint64_t blocks = (waves + kWavesPerBlock - 1) / kWavesPerBlock;
-    if (blocks > kMaxBlocks) {
-        const uint64_t h = n / 2;
-        auto from = [&](auto *p) { return p ? p + h : nullptr; };
-        const hipError_t e = launch_gather_slots(s, cache, payload, ids, sg, soff, h, out, err, stream);
-        return e != hipSuccess ? e
-                               : launch_gather_slots(s, cache, payload, from(ids), from(sg), from(soff), n - h,
-                                                     o + h * s.W, err, stream);
-    }
+    const uint64_t blocks = blocks_of_waves(waves);
+    if (too_many_blocks(blocks, n))
+        return in_halves(n, [&](uint64_t i, uint64_t count) {
+            return launch_gather_slots(s, cache, payload, from(ids, i), from(sg, i), from(soff, i), count, o + i * s.W,
+                                       err, stream);
+        });
     const dim3 grid((unsigned)blocks), block(kBlock);
     auto go = [&](auto k, auto tiled, auto src, auto split) {
         constexpr int K = decltype(k)::value, SRC = decltype(src)::value;

@@ -19,8 +19,29 @@ inline constexpr int kWavesPerBlock = 4;
 inline constexpr int kBlock = kWave * kWavesPerBlock;
 
 // Blocks of one launch: a grid's threads are counted in 32 bits, and one of 2^32 or more runs
-// short without an error. A launcher whose waves take few rows halves a call that has more.
+// short without an error. A launcher halves a call that has more (in_halves).
 inline constexpr uint64_t kMaxBlocks = 0xFFFFFFFFull / kBlock;
+
+// kMaxBlocks, or less while the library was loaded with the environment variable
+// IBP_TEST_MAX_BLOCKS set: a test hook, with which small calls take several launches too.
+uint64_t max_blocks();
+
+// Whether a call of n rows has to be halved: its launch would have too many blocks.
+inline bool too_many_blocks(uint64_t blocks, uint64_t n) { return blocks > max_blocks() && n > 1; }
+
+// A call of n rows as two: part(first row, rows) for each half, to the first that fails.
+template <class Part>
+auto in_halves(uint64_t n, const Part &part) -> decltype(part(n, n)) {
+    const uint64_t h = n / 2;
+    const auto e = part(0, h);
+    return e != decltype(e){} ? e : part(h, n - h);
+}
+
+// An optional array from its i-th element on.
+template <class T>
+T *from(T *p, uint64_t i) {
+    return p ? p + i : nullptr;
+}
 
 inline uint64_t blocks_of_waves(uint64_t waves) { return (waves + kWavesPerBlock - 1) / kWavesPerBlock; }
 

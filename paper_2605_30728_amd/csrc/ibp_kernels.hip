@@ -24,6 +24,7 @@
 //     sub-dword loads. No MFMA anywhere: nothing here is a contraction.
 #include <algorithm>
 #include <atomic>
+#include <cstdlib>
 #include <type_traits>
 
 #include "ibp_device.hpp"
@@ -1000,6 +1001,12 @@ template <int K, int MAXR>
 hipError_t launch_part_k(const DevStream &s, const uint32_t *p, uint64_t pay_base, const int64_t *ids,
                          const uint32_t *sg, const uint32_t *soff, uint64_t first, uint64_t n, uint32_t *o,
                          unsigned long long *err, hipStream_t stream) {
+    auto halves = [&] {
+        return in_halves(n, [&](uint64_t i, uint64_t count) {
+            return launch_part_k<K, MAXR>(s, p, pay_base, from(ids, i), from(sg, i), from(soff, i), first + i, count,
+                                          o + i * s.W, err, stream);
+        });
+    };
     if (s.W <= (uint32_t)(kWave * K)) {
         // rows of one tile of 129 to 512 words: batches of RB rows, 1-2 batches per wave (2
         // when there is work for ~16k waves: a wave's lookup and its batches are dependent
@@ -1008,8 +1015,9 @@ hipError_t launch_part_k(const DevStream &s, const uint32_t *p, uint64_t pay_bas
         const uint32_t nb = (uint32_t)std::max<uint64_t>(1, std::min<uint64_t>(2, n / (16384ull * RB)));
         const uint32_t seg = RB * nb;
         if (seg > (uint32_t)kWave) return hipErrorInvalidValue;   // lane i holds item i
-        const uint64_t waves = (n + seg - 1) / seg;
-        const dim3 grid((unsigned)((waves + kWavesPerBlock - 1) / kWavesPerBlock)), block(kBlock);
+        const uint64_t blocks = blocks_of_waves((n + seg - 1) / seg);
+        if (too_many_blocks(blocks, n)) return halves();
+        const dim3 grid((unsigned)blocks), block(kBlock);
         // participation dwords prefetched with the lookup: 1 for at most 32 chunks, 2 for
         // at most 64, else loaded per batch
         const uint32_t chunks = s.W / s.part_m;
@@ -1046,8 +1054,9 @@ hipError_t launch_part_k(const DevStream &s, const uint32_t *p, uint64_t pay_bas
     // rows of several tiles (only at eight words per lane): one row at a time per wave
     if constexpr (K == 8) {
         const uint32_t per_wave = (uint32_t)std::max<uint64_t>(1, std::min<uint64_t>(16, n / 16384));
-        const uint64_t waves = (n + per_wave - 1) / per_wave;
-        const dim3 grid((unsigned)((waves + kWavesPerBlock - 1) / kWavesPerBlock)), block(kBlock);
+        const uint64_t blocks = blocks_of_waves((n + per_wave - 1) / per_wave);
+        if (too_many_blocks(blocks, n)) return halves();
+        const dim3 grid((unsigned)blocks), block(kBlock);
         if (ids)
             hipLaunchKernelGGL((k_part_rows<K, MAXR, kSrcIds>), grid, block, 0, stream, s, p, pay_base, ids, sg, soff,
                                first, n, o, per_wave, err);
@@ -1080,7 +1089,15 @@ uint32_t compute_units() {
     return cu;
 }
 
+const uint64_t g_max_blocks = [] {
+    const char *e = std::getenv("IBP_TEST_MAX_BLOCKS");
+    const uint64_t n = e ? std::strtoull(e, nullptr, 10) : 0;
+    return n ? std::min(n, kMaxBlocks) : kMaxBlocks;
+}();
+
 }  // namespace
+
+uint64_t max_blocks() { return g_max_blocks; }
 
 uint64_t div_magic(uint32_t G) {
     if (G <= 1) return 0;
@@ -1121,13 +1138,11 @@ hipError_t launch_decompress(const DevStream &s, const uint8_t *payload, uint64_
     const int k = tiled ? 2 : words_per_lane(s.W);
     const RowSlices units = decompress_slices(first, n, s.G, k, tiles);
     const uint64_t blocks = blocks_of_waves(units.count * tiles);
-    if (blocks > kMaxBlocks && n > 1) {
-        const uint64_t h = n / 2;
-        const hipError_t e = launch_decompress(s, payload, pay_base, out, first, h, stream);
-        return e != hipSuccess ? e
-                               : launch_decompress(s, payload, pay_base, static_cast<uint32_t *>(out) + h * s.W,
-                                                   first + h, n - h, stream);
-    }
+    if (too_many_blocks(blocks, n))
+        return in_halves(n, [&](uint64_t i, uint64_t count) {
+            return launch_decompress(s, payload, pay_base, static_cast<uint32_t *>(out) + i * s.W, first + i, count,
+                                     stream);
+        });
     const auto *p = reinterpret_cast<const uint32_t *>(payload);
     auto *o = static_cast<uint32_t *>(out);
     dim3 grid((unsigned)blocks), block(kBlock);
@@ -1164,9 +1179,15 @@ hipError_t launch_gather(const DevStream &s, const uint8_t *payload, const int64
     const auto *p = reinterpret_cast<const uint32_t *>(payload);
     auto *o = static_cast<uint32_t *>(out);
     const int k = words_per_lane(s.W);
+    auto halves = [&] {
+        return in_halves(n, [&](uint64_t i, uint64_t count) {
+            return launch_gather(s, payload, from(ids, i), from(sg, i), from(soff, i), count, o + i * s.W, err, stream);
+        });
+    };
     if (s.W > 512) {
         const uint32_t seg = 16;
-        const uint64_t blocks = ((n + seg - 1) / seg + kWavesPerBlock - 1) / kWavesPerBlock;
+        const uint64_t blocks = blocks_of_waves((n + seg - 1) / seg);
+        if (too_many_blocks(blocks, n)) return halves();
         if (soff)
             hipLaunchKernelGGL((k_gather_tiled<8, 1, true>), dim3((unsigned)blocks), dim3(kBlock), 0, stream, s, p,
                                ids, sg, soff, n, o, seg, err);
@@ -1187,7 +1208,8 @@ hipError_t launch_gather(const DevStream &s, const uint8_t *payload, const int64
     while (nb < 4 && n / ((uint64_t)rb_sel * nb * 2) >= min_waves) nb *= 2;
     const uint32_t seg = (uint32_t)rb_sel * nb;
     if (seg > (uint32_t)kWave) return hipErrorInvalidValue;   // lane i holds request i
-    const uint64_t blocks = ((n + seg - 1) / seg + kWavesPerBlock - 1) / kWavesPerBlock;
+    const uint64_t blocks = blocks_of_waves((n + seg - 1) / seg);
+    if (too_many_blocks(blocks, n)) return halves();
     dim3 grid((unsigned)blocks), block(kBlock);
     auto go = [&](auto kk, auto rb) {
         constexpr int KK = decltype(kk)::value, R = decltype(rb)::value;

@@ -263,16 +263,12 @@ hipError_t launch_narrow_k(const DevStream &s, const uint8_t *payload, uint64_t 
     const uint32_t nb = n / ((K == 1 ? 16384ull : 8192ull) * RB) >= 1 && (K == 2 || one) ? 2 : 1;
     const uint32_t seg = RB * nb;
     const uint64_t waves = (n + seg - 1) / seg;
-    const uint64_t blocks = (waves + kWavesPerBlock - 1) / kWavesPerBlock;
-    if (blocks > kMaxBlocks) {
-        const uint64_t h = n / 2;
-        auto from = [&](auto *p) { return p ? p + h : nullptr; };
-        const hipError_t e =
-            launch_narrow_k<K, MAXR>(s, payload, pay_base, ids, sg, soff, first, h, o, err, stream);
-        return e != hipSuccess ? e
-                               : launch_narrow_k<K, MAXR>(s, payload, pay_base, from(ids), from(sg), from(soff),
-                                                          first + h, n - h, o + h * s.W, err, stream);
-    }
+    const uint64_t blocks = blocks_of_waves(waves);
+    if (too_many_blocks(blocks, n))
+        return in_halves(n, [&](uint64_t i, uint64_t count) {
+            return launch_narrow_k<K, MAXR>(s, payload, pay_base, from(ids, i), from(sg, i), from(soff, i), first + i,
+                                            count, o + i * s.W, err, stream);
+        });
     const dim3 grid((unsigned)blocks), block(kBlock);
     const uint32_t chunks = s.W / s.part_m;
     auto go = [&](auto pre, auto one_tag, auto src) {
