@@ -86,9 +86,13 @@ IBP_HD void slice_of(const RowSlices &u, uint32_t i, uint64_t &group, uint32_t &
 // of rows; every slice repeats its cluster's setup, which is small next to its rows. Measured:
 // 524,288 rows of 64 words 42.4 us with 32 rows per wave (16k waves), 40.5 with 8; 2,097,152
 // rows 160.5 and 154; 50k rows of 600 words in tiles 45.4 us at 16k waves and 47.9 at 32k.
-inline RowSlices decompress_slices(uint64_t first, uint64_t n, uint32_t G, int K, uint32_t tiles) {
+// From pinned host memory neighbouring rows share the lines that a wave reads over PCIe: 16k
+// waves at any width but one word per lane, there 512 (20,000 rows of 256 B 79.8 us in slices
+// of 8 rows and 71.9 in whole clusters of 32, 93,750 rows 334 and 325; 20,000 of 128 B 46.4 and
+// 40.7; 2,000 rows of 256 B 11.9 in 8 and 12.7 in 32).
+inline RowSlices decompress_slices(uint64_t first, uint64_t n, uint32_t G, int K, uint32_t tiles, bool host) {
     const uint32_t min_rows = K == 1 ? 8 : (K == 2 ? 4 : (K == 4 ? 2 : 1));
-    const uint64_t enough = K == 1 ? 131072 : 16384;
+    const uint64_t enough = K > 1 ? 16384 : (host ? 512 : 131072);
     uint32_t rows = std::min<uint32_t>(G, 64);
     while (rows > min_rows && row_slices(first, n, G, rows).count * tiles < enough)
         rows = ((rows + 1) / 2 + min_rows - 1) / min_rows * min_rows;

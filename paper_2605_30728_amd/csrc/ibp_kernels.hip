@@ -41,15 +41,21 @@ namespace {
 // payload byte where row i's packed bits start and `at.out(i)` the row's output; both are
 // wave-uniform. All loads of the batch are issued before any word is rebuilt, so RB*K loads
 // are in flight per wave. NR >= 0 applies NR precomputed runs per word; NR < 0 takes the
-// generic loop. A row is stored through a buffer descriptor of its own, whose range check
-// drops the lanes past the row's end and, with an empty range, the rows past n (which repeat
-// the last row's loads), without branches; non-temporally: with three output buffers in turn
-// 42.0 us against 46.7 with plain stores (bf16 KV layer, 134 MB out, 16-row batches), with
+// generic loop.
+//
+// A slice in device memory stores a row through a buffer descriptor of its own, whose range
+// check drops the lanes past the row's end and, with an empty range, the rows past n (which
+// repeat the last row's loads), without branches; non-temporally: with three output buffers in
+// turn 42.0 us against 46.7 with plain stores (bf16 KV layer, 134 MB out, 16-row batches), with
 // one buffer that every call writes again, whose lines plain stores find in the last-level
 // cache, 41.6 against 40.3 (exec-masked plain stores before: 48.9 and 42.1; now 40.0 and 40.5).
+// A slice of rows of at most 128 words in pinned host memory (At::kMaskedStores) takes plain
+// stores under the row's lane mask: 24 MB out of 512-B rows 184 us with those and 189 through
+// descriptors, of 128-B rows 359 and 372.
 template <int NR, int RB, bool PART, int K, int MAXR, class At>
 __device__ __forceinline__ void decode_batch(const Tile<K, MAXR> &t, const uint32_t *__restrict__ pay32,
                                              const At &at, uint32_t n, uint32_t W, uint32_t w0) {
+    constexpr bool kMasked = At::kMaskedStores && K <= 2;
     const uint32_t l = lane_id();
     uint32_t d0[RB][K], d1[RB][K], b[RB][K];
 #pragma unroll
@@ -70,28 +76,35 @@ __device__ __forceinline__ void decode_batch(const Tile<K, MAXR> &t, const uint3
     }
 #pragma unroll
     for (int i = 0; i < RB; ++i) {
-        const __amdgpu_buffer_rsrc_t o = row_rsrc(at.out(i) + w0, PART && i >= (int)n ? 0u : (W - w0) * 4u);
+        [[maybe_unused]] __amdgpu_buffer_rsrc_t o;
+        if constexpr (!kMasked) o = row_rsrc(at.out(i) + w0, PART && i >= (int)n ? 0u : (W - w0) * 4u);
 #pragma unroll
         for (int j = 0; j < K; ++j) {
             const uint32_t x = __builtin_amdgcn_alignbit(d1[i][j], d0[i][j], b[i][j]);
             uint32_t v;
             if constexpr (NR >= 0) v = word_fast<NR>(t, j, x);
             else v = word_generic(t.bv[j], t.nm[j], x);
-            const uint32_t one[1] = {v};
-            store_words<1>(o, (l + kWave * j) * 4u, one);
+            if constexpr (kMasked) {
+                static_assert(!PART, "partial batches store through descriptors");
+                const uint32_t w = w0 + l + kWave * j;
+                if (w < W) at.out(i)[w] = v;
+            } else {
+                const uint32_t one[1] = {v};
+                store_words<1>(o, (l + kWave * j) * 4u, one);
+            }
         }
     }
 }
 
 // Decode rows [0, n) of one cluster with the run count fixed at compile time: in full
-// batches, then the rest in a partial one (K = 1) or one by one (a partial batch of a few
-// rows measured 2% slower on wide rows, whose slices are whole batches but for a cluster's
-// last one).
+// batches, then the rest in a partial one (K = 1, device memory) or one by one (a partial
+// batch of a few rows measured 2% slower on wide rows, whose slices are whole batches but for
+// a cluster's last one).
 template <int NR, int K, int MAXR, class At>
 __device__ __forceinline__ void decode_rows_nr(const Tile<K, MAXR> &t, const uint32_t *__restrict__ pay32,
                                                uint32_t n, const At &at, uint32_t W, uint32_t w0) {
     constexpr int RB = K <= 1 ? 8 : (K <= 2 ? 4 : (K <= 4 ? 2 : 1));
-    constexpr int TAIL = K <= 1 ? RB : 1;
+    constexpr int TAIL = K <= 1 && !At::kMaskedStores ? RB : 1;
     uint32_t k = 0;
     for (; k + RB <= n; k += RB) decode_batch<NR, RB, false>(t, pay32, at.shifted(k), RB, W, w0);
     if constexpr (RB > 1)
@@ -117,7 +130,7 @@ __device__ __forceinline__ void decode_rows(const Tile<K, MAXR> &t, const uint32
 // PCIe twice; measured on a zero-copy KV layer, 0.94 merged against 0.89 split of CR x raw).
 template <bool SPLIT>
 struct SliceAt {
-    static constexpr bool kSplit = SPLIT;
+    static constexpr bool kSplit = SPLIT, kMaskedStores = !SPLIT;
     uint64_t base, rb;
     uint32_t *out0;
     uint32_t W;
@@ -129,7 +142,7 @@ struct SliceAt {
 // Rows of a run of gathered ids from one cluster: the row index inside the cluster
 // (or the staged byte offset) of request i0+i sits in lane i0+i of `rloc`.
 struct GatherAt {
-    static constexpr bool kSplit = false;
+    static constexpr bool kSplit = false, kMaskedStores = false;
     uint64_t base, rb;       // cluster payload byte and packed row bytes (device payload)
     uint32_t *seg_out;       // output row of request 0 of the wave's segment
     uint32_t W;
@@ -1136,7 +1149,7 @@ hipError_t launch_decompress(const DevStream &s, const uint8_t *payload, uint64_
     const bool tiled = s.tile_bits && !s.payload_host;
     const uint32_t tiles = tiled ? s.tiles128 : 1;
     const int k = tiled ? 2 : words_per_lane(s.W);
-    const RowSlices units = decompress_slices(first, n, s.G, k, tiles);
+    const RowSlices units = decompress_slices(first, n, s.G, k, tiles, s.payload_host);
     const uint64_t blocks = blocks_of_waves(units.count * tiles);
     if (too_many_blocks(blocks, n))
         return in_halves(n, [&](uint64_t i, uint64_t count) {

@@ -16,13 +16,13 @@ SHIM = r"""
 using namespace ibp::dev;
 extern "C" {
 uint64_t max_blocks() { return kMaxBlocks; }
-uint64_t decompress_blocks(uint64_t first, uint64_t n, uint32_t G, int K, uint32_t tiles) {
-    return blocks_of_waves(decompress_slices(first, n, G, K, tiles).count * tiles);
+uint64_t decompress_blocks(uint64_t first, uint64_t n, uint32_t G, int K, uint32_t tiles, int host) {
+    return blocks_of_waves(decompress_slices(first, n, G, K, tiles, host).count * tiles);
 }
 uint64_t cluster_grid(uint64_t n_groups) { return cluster_blocks(n_groups); }
 uint64_t slices(uint64_t first, uint64_t n, uint32_t G, uint32_t rows) { return row_slices(first, n, G, rows).count; }
-uint64_t decompress_rows(uint64_t first, uint64_t n, uint32_t G, int K, uint32_t tiles) {
-    return decompress_slices(first, n, G, K, tiles).rows;
+uint64_t decompress_rows(uint64_t first, uint64_t n, uint32_t G, int K, uint32_t tiles, int host) {
+    return decompress_slices(first, n, G, K, tiles, host).rows;
 }
 // first row of unit i, which ends at the slice's, the cluster's or the range's end
 uint64_t unit_row(uint64_t first, uint64_t n, uint32_t G, uint32_t rows, uint32_t i) {
@@ -43,8 +43,8 @@ def grid(tmp_path_factory):
     subprocess.run(["g++", "-O1", "-std=c++17", "-shared", "-fPIC", f"-I{CSRC}", str(d / "shim.cpp"), "-o", so], check=True)
     lib = ctypes.CDLL(so)
     u64, u32, i32 = ctypes.c_uint64, ctypes.c_uint32, ctypes.c_int
-    for name, args in {"max_blocks": [], "cluster_grid": [u64], "decompress_blocks": [u64, u64, u32, i32, u32], "slices": [u64, u64, u32, u32],
-                       "decompress_rows": [u64, u64, u32, i32, u32], "unit_row": [u64, u64, u32, u32, u32]}.items():
+    for name, args in {"max_blocks": [], "cluster_grid": [u64], "decompress_blocks": [u64, u64, u32, i32, u32, i32], "slices": [u64, u64, u32, u32],
+                       "decompress_rows": [u64, u64, u32, i32, u32, i32], "unit_row": [u64, u64, u32, u32, u32]}.items():
         getattr(lib, name).argtypes = args
         getattr(lib, name).restype = u64
     return lib
@@ -67,17 +67,18 @@ def test_units_cover_a_range_once(grid):
         assert at == first + n, (first, n, G, rows)
 
 
+@pytest.mark.parametrize("host", [0, 1])
 @pytest.mark.parametrize("W", [16, 100, 256, 1024, 2048])
 @pytest.mark.parametrize("G", [1 << 20, 1 << 28, 1 << 29, 1 << 31, (1 << 32) - 1])
-def test_decompress_blocks_follow_the_rows(grid, W, G):
-    K, tiles = (1, 1) if W <= 64 else (2, 1) if W <= 128 else (2, (W + 127) // 128)
+def test_decompress_blocks_follow_the_rows(grid, W, G, host):
+    K, tiles = (1, 1) if W <= 64 else (2, 1) if W <= 128 else (4 if W <= 256 else 8, 1) if host else (2, (W + 127) // 128)
     for first, n in ((0, 1000), (5, 900), (0, 1), (999, 1), (0, 50_000_000)):
-        blocks = grid.decompress_blocks(first, n, G, K, tiles)
-        rows = grid.decompress_rows(first, n, G, K, tiles)
+        blocks = grid.decompress_blocks(first, n, G, K, tiles, host)
+        rows = grid.decompress_rows(first, n, G, K, tiles, host)
         assert 1 <= blocks <= ((n - 1) // rows + 2) * tiles // 4 + 1, (first, n, rows)
     # halving a call reaches one launch's blocks, wherever a whole table starts
     n = 1 << 36
-    while grid.decompress_blocks(3, n, G, K, tiles) > grid.max_blocks():
+    while grid.decompress_blocks(3, n, G, K, tiles, host) > grid.max_blocks():
         n //= 2
     assert n >= 1 << 20
 
