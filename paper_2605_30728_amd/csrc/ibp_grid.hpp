@@ -80,22 +80,45 @@ IBP_HD void slice_of(const RowSlices &u, uint32_t i, uint64_t &group, uint32_t &
     }
 }
 
-// The slices of a contiguous decompress, each decoded by `tiles` waves of K words per lane: a
-// whole cluster (at most 64 rows), halved in whole batches while the launch would have fewer
-// than 16k waves (2 per wave slot of the chip; 128k at one word per lane), down to one batch
-// of rows; every slice repeats its cluster's setup, which is small next to its rows. Measured:
-// 524,288 rows of 64 words 42.4 us with 32 rows per wave (16k waves), 40.5 with 8; 2,097,152
-// rows 160.5 and 154; 50k rows of 600 words in tiles 45.4 us at 16k waves and 47.9 at 32k.
+// The slices of a contiguous decompress of rows of W words, each decoded by `tiles` waves of K
+// words per lane. A slice repeats its cluster's setup, so it should hold many rows; but many
+// rows per wave leave few waves, whose loads have to hide one another's latency. So a slice is
+// a whole cluster (at most 64 rows), halved in whole batches while the launch has too few waves.
+// Measured, us:
+//   W <= 32  the setup weighs most (a row is little work): down to 16 rows for 16k waves, to 8
+//            for 4k. 134 MB out of 64-B rows 110 with 8 rows, 78 with 16, 65 with 32; of
+//            128-B rows 55, 41 and 38; 31k rows of 128 B 4.3 with 8 and 4.7 with 32
+//   W <= 48  16 rows for 8k waves, else 8: 134 MB out of 160-B rows 46, 40 and 43 with 8, 16, 32
+//   W <= 64  8 rows: 524k rows of 256 B 40.5, 42.4 with 32
+//   W <= 128 8 rows for 2k waves, else 4: 134 MB out of 400-B rows 38 with 4, 34.5 with 8, 38
+//            with 16; 5k rows 3.6 with 4 and 3.75 with 8
+//   tiles    down to 4 rows for 16k waves (50k rows of 600 words 45.4, 47.9 for 32k waves)
 // From pinned host memory neighbouring rows share the lines that a wave reads over PCIe: 16k
 // waves at any width but one word per lane, there 512 (20,000 rows of 256 B 79.8 us in slices
 // of 8 rows and 71.9 in whole clusters of 32, 93,750 rows 334 and 325; 20,000 of 128 B 46.4 and
 // 40.7; 2,000 rows of 256 B 11.9 in 8 and 12.7 in 32).
-inline RowSlices decompress_slices(uint64_t first, uint64_t n, uint32_t G, int K, uint32_t tiles, bool host) {
-    const uint32_t min_rows = K == 1 ? 8 : (K == 2 ? 4 : (K == 4 ? 2 : 1));
-    const uint64_t enough = K > 1 ? 16384 : (host ? 512 : 131072);
+inline RowSlices decompress_slices(uint64_t first, uint64_t n, uint32_t G, uint32_t W, int K, uint32_t tiles,
+                                   bool host) {
+    const uint32_t batch = K == 1 ? 8 : (K == 2 ? 4 : (K == 4 ? 2 : 1));
     uint32_t rows = std::min<uint32_t>(G, 64);
-    while (rows > min_rows && row_slices(first, n, G, rows).count * tiles < enough)
-        rows = ((rows + 1) / 2 + min_rows - 1) / min_rows * min_rows;
+    auto halve = [&](uint32_t least, uint64_t waves) {
+        while (rows > least && row_slices(first, n, G, rows).count * tiles < waves)
+            rows = ((rows + 1) / 2 + batch - 1) / batch * batch;
+    };
+    if (host || tiles > 1) {
+        halve(batch, host && K == 1 ? 512 : 16384);
+    } else if (W <= 32) {
+        halve(16, 16384);
+        halve(8, 4096);
+    } else if (W <= 48) {
+        rows = std::min(rows, 16u);
+        halve(8, 8192);
+    } else if (W <= 64) {
+        rows = std::min(rows, 8u);
+    } else {
+        rows = std::min(rows, 8u);
+        halve(4, 2048);
+    }
     return row_slices(first, n, G, rows);
 }
 

@@ -1149,7 +1149,7 @@ hipError_t launch_decompress(const DevStream &s, const uint8_t *payload, uint64_
     const bool tiled = s.tile_bits && !s.payload_host;
     const uint32_t tiles = tiled ? s.tiles128 : 1;
     const int k = tiled ? 2 : words_per_lane(s.W);
-    const RowSlices units = decompress_slices(first, n, s.G, k, tiles, s.payload_host);
+    const RowSlices units = decompress_slices(first, n, s.G, s.W, k, tiles, s.payload_host);
     const uint64_t blocks = blocks_of_waves(units.count * tiles);
     if (too_many_blocks(blocks, n))
         return in_halves(n, [&](uint64_t i, uint64_t count) {

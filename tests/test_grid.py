@@ -16,13 +16,13 @@ SHIM = r"""
 using namespace ibp::dev;
 extern "C" {
 uint64_t max_blocks() { return kMaxBlocks; }
-uint64_t decompress_blocks(uint64_t first, uint64_t n, uint32_t G, int K, uint32_t tiles, int host) {
-    return blocks_of_waves(decompress_slices(first, n, G, K, tiles, host).count * tiles);
+uint64_t decompress_blocks(uint64_t first, uint64_t n, uint32_t G, uint32_t W, int K, uint32_t tiles, int host) {
+    return blocks_of_waves(decompress_slices(first, n, G, W, K, tiles, host).count * tiles);
 }
 uint64_t cluster_grid(uint64_t n_groups) { return cluster_blocks(n_groups); }
 uint64_t slices(uint64_t first, uint64_t n, uint32_t G, uint32_t rows) { return row_slices(first, n, G, rows).count; }
-uint64_t decompress_rows(uint64_t first, uint64_t n, uint32_t G, int K, uint32_t tiles, int host) {
-    return decompress_slices(first, n, G, K, tiles, host).rows;
+uint64_t decompress_rows(uint64_t first, uint64_t n, uint32_t G, uint32_t W, int K, uint32_t tiles, int host) {
+    return decompress_slices(first, n, G, W, K, tiles, host).rows;
 }
 // first row of unit i, which ends at the slice's, the cluster's or the range's end
 uint64_t unit_row(uint64_t first, uint64_t n, uint32_t G, uint32_t rows, uint32_t i) {
@@ -43,8 +43,8 @@ def grid(tmp_path_factory):
     subprocess.run(["g++", "-O1", "-std=c++17", "-shared", "-fPIC", f"-I{CSRC}", str(d / "shim.cpp"), "-o", so], check=True)
     lib = ctypes.CDLL(so)
     u64, u32, i32 = ctypes.c_uint64, ctypes.c_uint32, ctypes.c_int
-    for name, args in {"max_blocks": [], "cluster_grid": [u64], "decompress_blocks": [u64, u64, u32, i32, u32, i32], "slices": [u64, u64, u32, u32],
-                       "decompress_rows": [u64, u64, u32, i32, u32, i32], "unit_row": [u64, u64, u32, u32, u32]}.items():
+    for name, args in {"max_blocks": [], "cluster_grid": [u64], "decompress_blocks": [u64, u64, u32, u32, i32, u32, i32], "slices": [u64, u64, u32, u32],
+                       "decompress_rows": [u64, u64, u32, u32, i32, u32, i32], "unit_row": [u64, u64, u32, u32, u32]}.items():
         getattr(lib, name).argtypes = args
         getattr(lib, name).restype = u64
     return lib
@@ -73,14 +73,24 @@ def test_units_cover_a_range_once(grid):
 def test_decompress_blocks_follow_the_rows(grid, W, G, host):
     K, tiles = (1, 1) if W <= 64 else (2, 1) if W <= 128 else (4 if W <= 256 else 8, 1) if host else (2, (W + 127) // 128)
     for first, n in ((0, 1000), (5, 900), (0, 1), (999, 1), (0, 50_000_000)):
-        blocks = grid.decompress_blocks(first, n, G, K, tiles, host)
-        rows = grid.decompress_rows(first, n, G, K, tiles, host)
+        blocks = grid.decompress_blocks(first, n, G, W, K, tiles, host)
+        rows = grid.decompress_rows(first, n, G, W, K, tiles, host)
         assert 1 <= blocks <= ((n - 1) // rows + 2) * tiles // 4 + 1, (first, n, rows)
     # halving a call reaches one launch's blocks, wherever a whole table starts
     n = 1 << 36
-    while grid.decompress_blocks(3, n, G, K, tiles, host) > grid.max_blocks():
+    while grid.decompress_blocks(3, n, G, W, K, tiles, host) > grid.max_blocks():
         n //= 2
     assert n >= 1 << 20
+
+
+@pytest.mark.parametrize("W,n,rows", [(16, 2_000_000, 32), (16, 300_000, 16), (16, 30_000, 8), (32, 1_000_000, 32),
+                                      (32, 200_000, 16), (32, 60_000, 8), (33, 1_000_000, 16), (48, 1_000_000, 16),
+                                      (48, 100_000, 8), (49, 1_000_000, 8), (64, 3_000, 8), (65, 20_000, 8),
+                                      (128, 300_000, 8), (128, 10_000, 4)])
+def test_narrow_rows_keep_their_setup(grid, W, n, rows):
+    """Rows per slice of a payload in device memory: a narrow row is too little work to repeat
+    its cluster's setup every 8 rows, except where whole clusters leave few waves."""
+    assert grid.decompress_rows(0, n, 32, W, 1 if W <= 64 else 2, 1, 0) == rows
 
 
 @pytest.mark.parametrize("n", [1, 4, 5, 1 << 20, (1 << 26) - 1, 1 << 26, (1 << 26) + 1, 1 << 33])
