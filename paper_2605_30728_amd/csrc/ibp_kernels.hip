@@ -37,30 +37,28 @@ namespace dev {
 namespace {
 
 
-// Decode rows 0 .. min(RB, n) - 1 of one cluster (n >= RB unless PART). `at.byte(i)` is the
-// payload byte where row i's packed bits start and `at.out(i)` the row's output; both are
-// wave-uniform. All loads of the batch are issued before any word is rebuilt, so RB*K loads
+// Decode rows 0 .. RB - 1 of one cluster. `at.byte(i)` is the payload byte where row i's packed
+// bits start and `at.out(i)` the row's output; both are wave-uniform. All loads of the batch are issued before any word is rebuilt, so RB*K loads
 // are in flight per wave. NR >= 0 applies NR precomputed runs per word; NR < 0 takes the
 // generic loop.
 //
 // A slice in device memory stores a row through a buffer descriptor of its own, whose range
-// check drops the lanes past the row's end and, with an empty range, the rows past n (which
-// repeat the last row's loads), without branches; non-temporally: with three output buffers in
-// turn 42.0 us against 46.7 with plain stores (bf16 KV layer, 134 MB out, 16-row batches), with
+// check drops the lanes past the row's end without a branch; non-temporally: with three output
+// buffers in turn 42.0 us against 46.7 with plain stores (bf16 KV layer, 134 MB out, 16-row batches), with
 // one buffer that every call writes again, whose lines plain stores find in the last-level
 // cache, 41.6 against 40.3 (exec-masked plain stores before: 48.9 and 42.1; now 40.0 and 40.5).
 // A slice of rows of at most 128 words in pinned host memory (At::kMaskedStores) takes plain
 // stores under the row's lane mask: 24 MB out of 512-B rows 184 us with those and 189 through
 // descriptors, of 128-B rows 359 and 372.
-template <int NR, int RB, bool PART, int K, int MAXR, class At>
+template <int NR, int RB, int K, int MAXR, class At>
 __device__ __forceinline__ void decode_batch(const Tile<K, MAXR> &t, const uint32_t *__restrict__ pay32,
-                                             const At &at, uint32_t n, uint32_t W, uint32_t w0) {
+                                             const At &at, uint32_t W, uint32_t w0) {
     constexpr bool kMasked = At::kMaskedStores && K <= 2;
     const uint32_t l = lane_id();
     uint32_t d0[RB][K], d1[RB][K], b[RB][K];
 #pragma unroll
     for (int i = 0; i < RB; ++i) {
-        const uint64_t rbyte = at.byte(PART ? min((uint32_t)i, n - 1) : (uint32_t)i);
+        const uint64_t rbyte = at.byte(i);
         const uint32_t *__restrict__ p = pay32 + (rbyte >> 2);
         const uint32_t bit0 = ((uint32_t)rbyte & 3u) * 8u;
 #pragma unroll
@@ -77,7 +75,7 @@ __device__ __forceinline__ void decode_batch(const Tile<K, MAXR> &t, const uint3
 #pragma unroll
     for (int i = 0; i < RB; ++i) {
         [[maybe_unused]] __amdgpu_buffer_rsrc_t o;
-        if constexpr (!kMasked) o = row_rsrc(at.out(i) + w0, PART && i >= (int)n ? 0u : (W - w0) * 4u);
+        if constexpr (!kMasked) o = row_rsrc(at.out(i) + w0, (W - w0) * 4u);
 #pragma unroll
         for (int j = 0; j < K; ++j) {
             const uint32_t x = __builtin_amdgcn_alignbit(d1[i][j], d0[i][j], b[i][j]);
@@ -85,7 +83,6 @@ __device__ __forceinline__ void decode_batch(const Tile<K, MAXR> &t, const uint3
             if constexpr (NR >= 0) v = word_fast<NR>(t, j, x);
             else v = word_generic(t.bv[j], t.nm[j], x);
             if constexpr (kMasked) {
-                static_assert(!PART, "partial batches store through descriptors");
                 const uint32_t w = w0 + l + kWave * j;
                 if (w < W) at.out(i)[w] = v;
             } else {
@@ -96,19 +93,28 @@ __device__ __forceinline__ void decode_batch(const Tile<K, MAXR> &t, const uint3
     }
 }
 
-// Decode rows [0, n) of one cluster with the run count fixed at compile time: in full
-// batches, then the rest in a partial one (K = 1, device memory) or one by one (a partial
-// batch of a few rows measured 2% slower on wide rows, whose slices are whole batches but for
-// a cluster's last one).
+// Decode rows [0, n) of one cluster with the run count fixed at compile time: in full batches,
+// then the rest one by one or, at one word per lane from device memory, in a last full batch
+// that ends at the last row (it decodes some rows twice; few rows in a batch of their own kind
+// cost more than that: 4,300 rows of 54 words from the middle of a cluster 5.6 us, 4.4 now).
 template <int NR, int K, int MAXR, class At>
 __device__ __forceinline__ void decode_rows_nr(const Tile<K, MAXR> &t, const uint32_t *__restrict__ pay32,
                                                uint32_t n, const At &at, uint32_t W, uint32_t w0) {
     constexpr int RB = K <= 1 ? 8 : (K <= 2 ? 4 : (K <= 4 ? 2 : 1));
-    constexpr int TAIL = K <= 1 && !At::kMaskedStores ? RB : 1;
-    uint32_t k = 0;
-    for (; k + RB <= n; k += RB) decode_batch<NR, RB, false>(t, pay32, at.shifted(k), RB, W, w0);
-    if constexpr (RB > 1)
-        for (; k < n; k += TAIL) decode_batch<NR, TAIL, (TAIL > 1)>(t, pay32, at.shifted(k), n - k, W, w0);
+    if constexpr (K <= 1 && !At::kMaskedStores) {
+        if (n >= RB) {
+            for (uint32_t k = 0;; k = min(k + RB, n - RB)) {
+                decode_batch<NR, RB>(t, pay32, at.shifted(k), W, w0);
+                if (k + RB >= n) return;
+            }
+        }
+        for (uint32_t k = 0; k < n; ++k) decode_batch<NR, 1>(t, pay32, at.shifted(k), W, w0);
+    } else {
+        uint32_t k = 0;
+        for (; k + RB <= n; k += RB) decode_batch<NR, RB>(t, pay32, at.shifted(k), W, w0);
+        if constexpr (RB > 1)
+            for (; k < n; ++k) decode_batch<NR, 1>(t, pay32, at.shifted(k), W, w0);
+    }
 }
 
 template <int K, int MAXR, class At>
