@@ -42,9 +42,9 @@ __global__ __launch_bounds__(kBlock) void k_cache_gather(DevStream s, CacheView 
     // byte address of the row's packed bits: the slab entry for a hit; for a miss the
     // cluster's payload offset, to which the row's index times its packed size is added
     // once the size is known from the Mask
-    uint64_t off_l = 0;
-    const bool hit = valid && cache_probe(c, uid, off_l);
-    if (!hit) off_l = s.index[g_l];
+    const CacheProbe probe = cache_probe_begin(c, uid);
+    uint64_t off_l = s.index[g_l];
+    const bool hit = valid && cache_probe_end(c, uid, probe, off_l);
     const uint32_t mul_l = hit ? 0u : r_l;
     const uint64_t nhit = __ballot(valid && hit), nmiss = __ballot(valid && !hit);
     const uint64_t bad = __ballot(l < cnt && !valid);

@@ -122,6 +122,8 @@ __device__ __forceinline__ void gather_slots(const DevStream &s, const CacheView
     uint32_t len;
     const uint8_t *slot_l;
     uint2 pair;
+    uint64_t uid = 0;
+    [[maybe_unused]] CacheProbe probe;
     if constexpr (SRC == kFromStage) {
         g = sg[r];
         byte = soff[r];
@@ -131,16 +133,14 @@ __device__ __forceinline__ void gather_slots(const DevStream &s, const CacheView
     } else {
         const int64_t id = ids[r];
         valid = id >= 0 && (uint64_t)id < s.n_rows;
-        const uint64_t uid = valid ? (uint64_t)id : 0;
+        uid = valid ? (uint64_t)id : 0;
+        if constexpr (SRC == kFromCache) probe = cache_probe_begin(c, uid);
         g = s.G == 1 ? uid : __umul64hi(uid, s.g_magic);
         slot_l = s.slots + g * s.slot_bytes;
         pair = reinterpret_cast<const uint2 *>(slot_l)[l % P];
         const GroupInfo gi = s.groups[g];
         byte = valid ? gi.off + (uint64_t)(uint32_t)(uid - g * s.G) * gi.stride : 0;
         len = valid ? gi.stride : 0u;   // (an invalid id reads nothing)
-        if constexpr (SRC == kFromCache) {
-            if (valid) hit = cache_probe(c, uid, byte);
-        }
     }
     // every item's pair indices of the lane's words, 4 bits each
     const uint8_t *const idx_l = slot_l + 8 * P + (TILED ? t * (32u * K) : 0u);
@@ -151,6 +151,10 @@ __device__ __forceinline__ void gather_slots(const DevStream &s, const CacheView
         if constexpr (K == 1) idx[i] = p[own_lane() >> 1];
         else if constexpr (K == 2) idx[i] = p[own_lane()];
         else idx[i] = *(const __attribute__((address_space(1))) uint16_t *)(p + 2u * own_lane());
+    }
+    if constexpr (SRC == kFromCache) {
+        keep_order();   // the probe's loop is entered with the loads above in flight
+        hit = valid && cache_probe_end(c, uid, probe, byte);
     }
     uint32_t start = 0;
     if constexpr (TILED) start = s.tile_bits[g * s.tiles128 + t * (K / 2)];
