@@ -55,15 +55,26 @@ struct RowSlices {
     uint64_t count;
 };
 
-// n >= 1, G >= 1, rows >= 1.
-inline RowSlices row_slices(uint64_t first, uint64_t n, uint32_t G, uint32_t rows) {
+// Rows [first, first + n) as the places of the first and the last in their clusters.
+// n >= 1, G >= 1.
+struct RowRange {
+    uint64_t g0, g1;       // clusters
+    uint32_t row0, row1;   // rows inside them
+};
+
+inline RowRange row_range(uint64_t first, uint64_t n, uint32_t G) {
+    const uint64_t last = first + n - 1, g0 = first / G, g1 = last / G;
+    return {g0, g1, (uint32_t)(first - g0 * G), (uint32_t)(last - g1 * G)};
+}
+
+// rows >= 1.
+inline RowSlices row_slices(const RowRange &r, uint32_t G, uint32_t rows) {
     RowSlices u;
-    const uint64_t last = first + n - 1, g1 = last / G;
-    u.g0 = first / G;
+    u.g0 = r.g0;
     u.rows = rows;
     u.per_group = (G - 1) / rows + 1;
-    u.skip = (uint32_t)((first - u.g0 * G) / rows);
-    u.count = (g1 - u.g0) * u.per_group + (last - g1 * G) / rows - u.skip + 1;
+    u.skip = r.row0 / rows;
+    u.count = (r.g1 - r.g0) * u.per_group + r.row1 / rows - u.skip + 1;
     return u;
 }
 
@@ -100,10 +111,12 @@ IBP_HD void slice_of(const RowSlices &u, uint32_t i, uint64_t &group, uint32_t &
 inline RowSlices decompress_slices(uint64_t first, uint64_t n, uint32_t G, uint32_t W, int K, uint32_t tiles,
                                    bool host) {
     const uint32_t batch = K == 1 ? 8 : (K == 2 ? 4 : (K == 4 ? 2 : 1));
+    const RowRange range = row_range(first, n, G);
     uint32_t rows = std::min<uint32_t>(G, 64);
+    auto few = [&](uint32_t r, uint64_t waves) { return row_slices(range, G, r).count * tiles < waves; };
     auto halve = [&](uint32_t least, uint64_t waves) {
-        while (rows > least && row_slices(first, n, G, rows).count * tiles < waves)
-            rows = ((rows + 1) / 2 + batch - 1) / batch * batch;
+        if (rows > least && few(least, waves)) rows = least;   // (a small call: no steps to it)
+        while (rows > least && few(rows, waves)) rows = ((rows + 1) / 2 + batch - 1) / batch * batch;
     };
     if (host || tiles > 1) {
         halve(batch, host && K == 1 ? 512 : 16384);
@@ -119,7 +132,7 @@ inline RowSlices decompress_slices(uint64_t first, uint64_t n, uint32_t G, uint3
         rows = std::min(rows, 8u);
         halve(4, 2048);
     }
-    return row_slices(first, n, G, rows);
+    return row_slices(range, G, rows);
 }
 
 // The waves of a kernel that takes a stream's clusters in strides of the grid: one per cluster,

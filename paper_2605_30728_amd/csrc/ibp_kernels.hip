@@ -190,51 +190,66 @@ __device__ __forceinline__ void decode_rows_tiled(const uint32_t *__restrict__ m
 }
 
 
+// What k_decompress needs of the stream and the call: 144 bytes of arguments with its two
+// pointers, and no implicit ones. A small call is bound by its launch on the host, which takes
+// longer with more of them: ns per call with the whole DevStream (200 bytes, 456 with the grid's
+// size as an implicit argument) -> with this, 1,903 rows of 32 words 2,513 -> 2,473, 282 rows of
+// 253 words 2,884 -> 2,733.
+struct RangeCall {
+    const uint32_t *meta;
+    const uint64_t *index;
+    const GroupInfo *groups;     // TILED
+    const uint32_t *tile_bits;   // TILED
+    uint64_t pay_base, first, end;
+    RowSlices units;
+    uint32_t W, G, row_align;
+    uint32_t tiles128, blocks;   // TILED
+};
+
 // One wave per unit = a slice of a cluster's rows (decompress_slices) or, TILED, (slice,
 // tile of 64K words): the cluster's tile table gives the bit at which the tile starts, so
 // the tiles of wide rows are as independent as narrow rows.
 template <int K, int MAXR, bool SPLIT, bool TILED>
-__global__ __launch_bounds__(kBlock) void k_decompress(DevStream s, const uint32_t *__restrict__ pay32,
-                                                        uint64_t pay_base, uint32_t *__restrict__ out,
-                                                        uint64_t first, uint64_t n, RowSlices units) {
+__global__ __launch_bounds__(kBlock) void k_decompress(RangeCall c, const uint32_t *__restrict__ pay32,
+                                                        uint32_t *__restrict__ out) {
     uint32_t unit = (uint32_t)wave_slot(), w0 = 0;
     if constexpr (TILED) {
         // the tiles of a slice side by side on one XCD: neighbours share a line of every row
-        const uint32_t slot = xcd_block(blockIdx.x, gridDim.x) * kWavesPerBlock +
+        const uint32_t slot = xcd_block(blockIdx.x, c.blocks) * kWavesPerBlock +
                               (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
-        unit = slot / s.tiles128;
-        w0 = (slot - unit * s.tiles128) * (kWave * K);
+        unit = slot / c.tiles128;
+        w0 = (slot - unit * c.tiles128) * (kWave * K);
     }
-    if (unit >= units.count) return;
+    if (unit >= c.units.count) return;
     uint64_t g;
     uint32_t slice;
-    slice_of(units, unit, g, slice);
-    const uint64_t gstart = g * s.G;
-    uint64_t r_lo = gstart + (uint64_t)slice * units.rows;
-    uint64_t r_hi = min(r_lo + units.rows, min(gstart + s.G, s.n_rows));
-    r_lo = max(r_lo, first);
-    r_hi = min(r_hi, first + n);
+    slice_of(c.units, unit, g, slice);
+    const uint64_t gstart = g * c.G;
+    uint64_t r_lo = gstart + (uint64_t)slice * c.units.rows;
+    const uint64_t r_hi = min(min(r_lo + c.units.rows, gstart + c.G), c.end);
+    r_lo = max(r_lo, c.first);
     if (r_lo >= r_hi) return;
-    const uint32_t W = s.W;
-    const uint32_t *__restrict__ mg = s.meta + g * 2ull * W;
-    const uint64_t base = s.index[g] - pay_base;
+    const uint32_t W = c.W;
+    const uint32_t *__restrict__ mg = c.meta + g * 2ull * W;
+    const uint64_t base = c.index[g] - c.pay_base;
     const uint32_t rows = (uint32_t)(r_hi - r_lo);
+    uint32_t *const out0 = out + (r_lo - c.first) * W;
     if constexpr (TILED) {
         static_assert(K == 2, "the tile table is of 128-word tiles");
         Tile<K, MAXR> t;
-        tile_setup(t, mg, W, w0, s.tile_bits[g * s.tiles128 + w0 / (kWave * K)]);
-        const uint64_t rb = s.groups[g].stride;
-        const SliceAt<SPLIT> at{base + (r_lo - gstart) * rb, rb, out + (r_lo - first) * W, W};
+        tile_setup(t, mg, W, w0, c.tile_bits[g * c.tiles128 + w0 / (kWave * K)]);
+        const uint64_t rb = c.groups[g].stride;
+        const SliceAt<SPLIT> at{base + (r_lo - gstart) * rb, rb, out0, W};
         decode_rows(t, pay32, rows, at, W, w0);
     } else if (W <= (uint32_t)(kWave * K)) {
         Tile<K, MAXR> t;
         tile_setup(t, mg, W, 0, 0);
-        const uint64_t rb = row_stride((t.bits + 7u) >> 3, s.row_align);
-        const SliceAt<SPLIT> at{base + (r_lo - gstart) * rb, rb, out + (r_lo - first) * W, W};
+        const uint64_t rb = row_stride((t.bits + 7u) >> 3, c.row_align);
+        const SliceAt<SPLIT> at{base + (r_lo - gstart) * rb, rb, out0, W};
         decode_rows(t, pay32, rows, at, W, 0);
     } else {
-        const uint64_t rb = row_stride((row_bits(mg, W) + 7u) >> 3, s.row_align);
-        const SliceAt<SPLIT> at{base + (r_lo - gstart) * rb, rb, out + (r_lo - first) * W, W};
+        const uint64_t rb = row_stride((row_bits(mg, W) + 7u) >> 3, c.row_align);
+        const SliceAt<SPLIT> at{base + (r_lo - gstart) * rb, rb, out0, W};
         decode_rows_tiled<K, MAXR>(mg, pay32, rows, at, W);
     }
 }
@@ -1165,10 +1180,12 @@ hipError_t launch_decompress(const DevStream &s, const uint8_t *payload, uint64_
     const auto *p = reinterpret_cast<const uint32_t *>(payload);
     auto *o = static_cast<uint32_t *>(out);
     dim3 grid((unsigned)blocks), block(kBlock);
+    const RangeCall call{s.meta,    s.index, s.groups, s.tile_bits, pay_base,    first,           first + n,
+                         units,     s.W,     s.G,      s.row_align, s.tiles128, (uint32_t)blocks};
     auto go = [&](auto kk, auto mr, auto split, auto tile) {
         constexpr int KK = decltype(kk)::value, MR = decltype(mr)::value;
         constexpr bool SP = decltype(split)::value, TI = decltype(tile)::value;
-        hipLaunchKernelGGL((k_decompress<KK, MR, SP, TI>), grid, block, 0, stream, s, p, pay_base, o, first, n, units);
+        hipLaunchKernelGGL((k_decompress<KK, MR, SP, TI>), grid, block, 0, stream, call, p, o);
     };
     // two dword loads per window from device memory, one 8-byte load from pinned host memory
     // (where a wave also takes whole rows: a tile's first and last lines would cross PCIe

@@ -20,13 +20,13 @@ uint64_t decompress_blocks(uint64_t first, uint64_t n, uint32_t G, uint32_t W, i
     return blocks_of_waves(decompress_slices(first, n, G, W, K, tiles, host).count * tiles);
 }
 uint64_t cluster_grid(uint64_t n_groups) { return cluster_blocks(n_groups); }
-uint64_t slices(uint64_t first, uint64_t n, uint32_t G, uint32_t rows) { return row_slices(first, n, G, rows).count; }
+uint64_t slices(uint64_t first, uint64_t n, uint32_t G, uint32_t rows) { return row_slices(row_range(first, n, G), G, rows).count; }
 uint64_t decompress_rows(uint64_t first, uint64_t n, uint32_t G, uint32_t W, int K, uint32_t tiles, int host) {
     return decompress_slices(first, n, G, W, K, tiles, host).rows;
 }
 // first row of unit i, which ends at the slice's, the cluster's or the range's end
 uint64_t unit_row(uint64_t first, uint64_t n, uint32_t G, uint32_t rows, uint32_t i) {
-    const RowSlices u = row_slices(first, n, G, rows);
+    const RowSlices u = row_slices(row_range(first, n, G), G, rows);
     uint64_t g; uint32_t s;
     slice_of(u, i, g, s);
     return g * G + (uint64_t)s * rows;
