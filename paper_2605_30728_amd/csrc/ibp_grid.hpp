@@ -105,9 +105,11 @@ IBP_HD void slice_of(const RowSlices &u, uint32_t i, uint64_t &group, uint32_t &
 //            with 16; 5k rows 3.6 with 4 and 3.75 with 8
 //   tiles    down to 4 rows for 16k waves (50k rows of 600 words 45.4, 47.9 for 32k waves)
 // From pinned host memory neighbouring rows share the lines that a wave reads over PCIe: 16k
-// waves at any width but one word per lane, there 512 (20,000 rows of 256 B 79.8 us in slices
+// waves at any width but 13 to 64 words, there 512 (20,000 rows of 256 B 79.8 us in slices
 // of 8 rows and 71.9 in whole clusters of 32, 93,750 rows 334 and 325; 20,000 of 128 B 46.4 and
-// 40.7; 2,000 rows of 256 B 11.9 in 8 and 12.7 in 32).
+// 40.7; 2,000 rows of 256 B 11.9 in 8 and 12.7 in 32). A few rows of up to 12 words fit one line
+// as it is: bf16 rows of 32 B, 163,840 of them 98.8 in 8 rows and 104.5 in 32; of 40 B, 131,072
+// 97.3 and 100.1; of 48 B 96.5 and 98.9; but of 56 B 58.3 and 55.3 (56,173 rows).
 inline RowSlices decompress_slices(uint64_t first, uint64_t n, uint32_t G, uint32_t W, int K, uint32_t tiles,
                                    bool host) {
     const uint32_t batch = K == 1 ? 8 : (K == 2 ? 4 : (K == 4 ? 2 : 1));
@@ -119,7 +121,7 @@ inline RowSlices decompress_slices(uint64_t first, uint64_t n, uint32_t G, uint3
         while (rows > least && few(rows, waves)) rows = ((rows + 1) / 2 + batch - 1) / batch * batch;
     };
     if (host || tiles > 1) {
-        halve(batch, host && K == 1 ? 512 : 16384);
+        halve(batch, host && K == 1 && W > 12 ? 512 : 16384);
     } else if (W <= 32) {
         halve(16, 16384);
         halve(8, 4096);

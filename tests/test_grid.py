@@ -93,6 +93,12 @@ def test_narrow_rows_keep_their_setup(grid, W, n, rows):
     assert grid.decompress_rows(0, n, 32, W, 1 if W <= 64 else 2, 1, 0) == rows
 
 
+@pytest.mark.parametrize("W,n,rows", [(1, 100_000, 8), (12, 100_000, 8), (12, 1_000_000, 32), (13, 100_000, 32),
+                                      (13, 10_000, 16), (64, 100_000, 32), (65, 20_000, 4)])
+def test_rows_in_host_memory_share_their_lines(grid, W, n, rows):
+    assert grid.decompress_rows(0, n, 32, W, 1 if W <= 64 else 2, 1, 1) == rows
+
+
 @pytest.mark.parametrize("n", [1, 4, 5, 1 << 20, (1 << 26) - 1, 1 << 26, (1 << 26) + 1, 1 << 33])
 def test_cluster_grid_is_bounded(grid, n):
     assert 1 <= grid.cluster_grid(n) <= min((n + 3) // 4, grid.max_blocks())
