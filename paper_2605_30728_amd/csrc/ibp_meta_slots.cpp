@@ -53,10 +53,12 @@ inline uint32_t rd32(const uint8_t *p) {
     return v;
 }
 
-// Distinct (Mask, Bitval) pairs of the cluster at mg, in order of first appearance, and
-// each word's pair index; stops (returning kMaxPairs + 1) at the first pair beyond
-// kMaxPairs.
-uint32_t cluster_pairs(const uint8_t *mg, uint32_t W, uint32_t *pm, uint32_t *pb, uint8_t *word_pair) {
+// Distinct (Mask, Bitval) pairs of the cluster at mg, in order of first appearance;
+// index(w, k) gets each word's pair. Stops (returning kMaxPairs + 1) at the first pair beyond
+// kMaxPairs. Allocates nothing: it runs on the pool's threads, where an exception would end
+// the process.
+template <class Index>
+uint32_t cluster_pairs(const uint8_t *mg, uint32_t W, uint32_t *pm, uint32_t *pb, const Index &index) {
     uint32_t n = 0;
     for (uint32_t w = 0; w < W; ++w) {
         const uint32_t m = rd32(mg + 4ull * w), b = rd32(mg + 4ull * (W + w));
@@ -68,7 +70,7 @@ uint32_t cluster_pairs(const uint8_t *mg, uint32_t W, uint32_t *pm, uint32_t *pb
             pb[n] = b;
             ++n;
         }
-        if (word_pair) word_pair[w] = (uint8_t)k;
+        index(w, k);
     }
     return n;
 }
@@ -84,7 +86,7 @@ uint32_t build_meta_slots(const uint8_t *meta, uint64_t n_groups, uint32_t W, ui
     pool.run(n_groups, block, [&](uint64_t lo, uint64_t hi) {
         uint32_t pm[kMaxPairs], pb[kMaxPairs], m = 0;
         for (uint64_t g = lo; g < hi && m <= kMaxPairs; ++g)
-            m = std::max(m, cluster_pairs(meta + g * raw, W, pm, pb, nullptr));
+            m = std::max(m, cluster_pairs(meta + g * raw, W, pm, pb, [](uint32_t, uint32_t) {}));
         uint32_t cur = most.load(std::memory_order_relaxed);
         while (m > cur && !most.compare_exchange_weak(cur, m, std::memory_order_relaxed)) {
         }
@@ -98,27 +100,17 @@ uint32_t build_meta_slots(const uint8_t *meta, uint64_t n_groups, uint32_t W, ui
     slots.assign(std::max<uint64_t>(n_groups, 1) * S, 0);
     // pass 2: the slots
     pool.run(n_groups, block, [&](uint64_t lo, uint64_t hi) {
-        std::vector<uint8_t> word_pair(W);
         uint32_t pm[kMaxPairs], pb[kMaxPairs];
         for (uint64_t g = lo; g < hi; ++g) {
-            uint8_t *slot = slots.data() + g * S;
-            const uint32_t n = cluster_pairs(meta + g * raw, W, pm, pb, word_pair.data());
+            uint8_t *slot = slots.data() + g * S, *idx = slot + 8ull * P;
+            const uint32_t n = cluster_pairs(meta + g * raw, W, pm, pb, [&](uint32_t w, uint32_t k) {
+                const uint64_t at = word_order ? w : (uint64_t)K * (w % 64) + w / 64;
+                idx[at >> 1] |= (uint8_t)(k << (4 * (at & 1)));
+            });
             for (uint32_t k = 0; k < n; ++k) {
                 std::memcpy(slot + 8ull * k, &pm[k], 4);
                 std::memcpy(slot + 8ull * k + 4, &pb[k], 4);
             }
-            uint8_t *idx = slot + 8ull * P;
-            if (word_order) {
-                for (uint32_t w = 0; w < W; ++w) idx[w >> 1] |= (uint8_t)(word_pair[w] << (4 * (w & 1)));
-                continue;
-            }
-            for (uint32_t l = 0; l < 64; ++l)
-                for (uint32_t j = 0; j < K; ++j) {
-                    const uint32_t w = l + 64 * j;
-                    const uint32_t k = w < W ? word_pair[w] : 0u;
-                    const uint64_t bit = 4ull * (K * l + j);
-                    idx[bit >> 3] |= (uint8_t)(k << (bit & 7));
-                }
         }
     });
     return P;

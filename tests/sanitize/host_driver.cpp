@@ -119,23 +119,26 @@ void check_slots(const std::vector<uint8_t> &stream, ibp::Pool &pool) {
     ibp_desc d{};
     if (ibp_describe(stream.data(), stream.size(), &d) != IBP_OK || d.flags != 0 || d.n_groups == 0) return;
     const uint32_t W = d.row_bytes / 4;
-    if (W > 512) return;
     const uint32_t K = W <= 64 ? 1 : W <= 128 ? 2 : W <= 256 ? 4 : 8;
     std::vector<uint8_t> slots;
     const uint8_t *meta = stream.data() + d.meta_off;
-    const uint32_t P = ibp::build_meta_slots(meta, d.n_groups, W, K, pool, slots);
-    if (!P) return;
-    const uint64_t S = ibp::meta_slot_bytes(P, K);
-    CHECK(slots.size() >= d.n_groups * S, "slot area");
-    for (uint64_t g = 0; g < d.n_groups; ++g) {
-        const uint8_t *slot = slots.data() + g * S, *mg = meta + g * 8ull * W;
-        for (uint32_t w = 0; w < W; ++w) {
-            const uint32_t l = w % 64, j = w / 64;
-            const uint64_t bit = 4ull * (K * l + j);
-            const uint32_t k = (slot[8ull * P + (bit >> 3)] >> (bit & 7)) & 15u;
-            CHECK(k < P, "pair index");
-            CHECK(std::memcmp(slot + 8ull * k, mg + 4ull * w, 4) == 0, "slot Mask g=%llu w=%u", (unsigned long long)g, w);
-            CHECK(std::memcmp(slot + 8ull * k + 4, mg + 4ull * (W + w), 4) == 0, "slot Bitval");
+    for (const bool word_order : {false, true}) {
+        if (!word_order && W > 512) continue;
+        const uint32_t P = ibp::build_meta_slots(meta, d.n_groups, W, K, pool, slots, word_order);
+        if (!P) return;
+        const uint64_t S = word_order ? ibp::meta_slot_bytes_of(P, W) : ibp::meta_slot_bytes(P, K);
+        CHECK(slots.size() >= d.n_groups * S, "slot area");
+        for (uint64_t g = 0; g < d.n_groups; ++g) {
+            const uint8_t *slot = slots.data() + g * S, *mg = meta + g * 8ull * W;
+            for (uint32_t w = 0; w < W; ++w) {
+                const uint32_t l = w % 64, j = w / 64;
+                const uint64_t bit = 4ull * (word_order ? w : K * l + j);
+                CHECK(8ull * P + (bit >> 3) < S, "index inside the slot");
+                const uint32_t k = (slot[8ull * P + (bit >> 3)] >> (bit & 7)) & 15u;
+                CHECK(k < P, "pair index");
+                CHECK(std::memcmp(slot + 8ull * k, mg + 4ull * w, 4) == 0, "slot Mask g=%llu w=%u", (unsigned long long)g, w);
+                CHECK(std::memcmp(slot + 8ull * k + 4, mg + 4ull * (W + w), 4) == 0, "slot Bitval");
+            }
         }
     }
 }
