@@ -12,7 +12,6 @@ namespace dev {
 struct GroupInfo {
     uint64_t off;      // byte of its first row
     uint32_t stride;   // bytes from one row to the next
-    uint32_t bits;     // packed bits of a row
 };
 
 // What the kernels need to know about a stream resident on the device.
@@ -30,10 +29,10 @@ struct DevStream {
                              // roundup(rb, row_align) bytes (0: every rb bytes, no padding)
     uint32_t payload_host;   // 1: the kernels read the payload in pinned host memory over
                              // PCIe (zero-copy placements), 0: device memory (payload or stage)
-    // clustered scheme, W <= 512, every cluster with at most 16 distinct (Mask, Bitval)
-    // pairs: the row gathers' compact metadata, one slot of slot_bytes per cluster holding
-    // slot_pairs (8 or 16) pairs and the 4-bit word indices (see load_row_meta); slots
-    // null: they read `meta`
+    // clustered scheme, every cluster with at most 16 distinct (Mask, Bitval) pairs, in lane
+    // order also W <= 512: the row gathers' compact metadata, one slot of slot_bytes per
+    // cluster holding slot_pairs (8 or 16) pairs and the 4-bit word indices (word order:
+    // launch_gather_slots; lane order: load_row_meta); slots null: they read `meta`
     const uint8_t *slots;
     uint32_t slot_pairs;
     uint32_t slot_bytes;
@@ -64,14 +63,15 @@ uint64_t div_magic(uint32_t G);
 // with K = 8.
 inline int words_per_lane(uint32_t W) { return W <= 64 ? 1 : W <= 128 ? 2 : W <= 256 ? 4 : 8; }
 
-// Bytes of a compact metadata slot holding `pairs` (Mask, Bitval) u32 pairs and the 4-bit
-// pair indices of rows decoded with K words per lane (32K bytes), padded to 128-byte lines.
-inline constexpr uint32_t meta_slot_bytes(uint32_t pairs, uint32_t K) { return (8 * pairs + 32 * K + 127) / 128 * 128; }
+// What the kernels may read past a payload's last packed byte (and from the first byte of an
+// empty one): a window is three dwords from any word's first bit, lanes past the row's words
+// included, and a thresholded row's participation bits are read as up to five dwords.
+inline constexpr uint32_t kReadPast = 20;
 
 // Rows [first, first + n) into out (row-major). Packed row r of group g is read at byte
 // off[g] - pay_base + (r - g*G) * rb_g of `payload` (participation scheme: at byte
-// off[r] - pay_base, off[r+1] - off[r] bytes), which must be readable for 8 bytes past
-// the last packed byte.
+// off[r] - pay_base, off[r+1] - off[r] bytes), which must be readable for kReadPast bytes
+// past the last packed byte.
 hipError_t launch_decompress(const DevStream &s, const uint8_t *payload, uint64_t pay_base,
                              void *out, uint64_t first, uint64_t n, hipStream_t stream);
 
@@ -80,7 +80,7 @@ hipError_t launch_decompress(const DevStream &s, const uint8_t *payload, uint64_
 // payload; ids outside [0, n_rows) give a zero row and one increment of *err.
 // Host-packed staging (ids null): request i belongs to cluster sg[i] (validated on the
 // host) and its packed bytes are [soff[i], soff[i+1]) of `payload` (soff has n + 1
-// entries). Either payload is readable 8 bytes past its last byte.
+// entries). Either payload is readable kReadPast bytes past its last byte.
 hipError_t launch_gather(const DevStream &s, const uint8_t *payload, const int64_t *ids,
                          const uint32_t *sg, const uint32_t *soff, uint64_t n, void *out,
                          unsigned long long *err, hipStream_t stream);
@@ -102,7 +102,7 @@ inline constexpr uint32_t kCountStride = 16;   // u64 per line
 // A compressed row cache resident on the device (see ibp_cache_kernels.hip).
 struct CacheView {
     const void *table;               // 2^log2cap slots of {u64 key = id + 1 (0 empty), u64 entry}
-    const uint8_t *slab;             // cached packed rows (readable 8 bytes past the last)
+    const uint8_t *slab;             // cached packed rows (readable kReadPast bytes past the last)
     const uint8_t *host_payload;     // device address of the pinned payload (misses)
     unsigned long long *counts;      // kCountLines x [hits, misses, unused...]
     uint64_t mask;                   // 2^log2cap - 1

@@ -162,7 +162,7 @@ __device__ __forceinline__ void gather_slots(const DevStream &s, const CacheView
     // first bit of the item
     const uint8_t *const row_l = (SRC == kFromCache && hit ? c.slab : pay) + (byte & ~3ull);
     const uint32_t bit0 = ((uint32_t)byte & 3u) * 8u;
-    // (at least 12 bytes, readable past any row, so that a window's split loads stay ordered
+    // (at least 12 bytes, readable past any row (kReadPast), so that a window's split loads stay ordered
     // against the range)
     const uint32_t range_l = max(((bit0 + len * 8u + 31u) >> 5) * 4u, 12u);
     const uint32_t first_l = bit0 + start;
@@ -349,7 +349,7 @@ __global__ __launch_bounds__(kBlock) void k_group_info(DevStream s, GroupInfo *_
             bits += wave_sum(n);
         }
         if (groups && l == 0)
-            groups[g] = GroupInfo{s.index[g], (uint32_t)row_stride((bits + 7u) >> 3, s.row_align), bits};
+            groups[g] = GroupInfo{s.index[g], (uint32_t)row_stride((bits + 7u) >> 3, s.row_align)};
     }
 }
 

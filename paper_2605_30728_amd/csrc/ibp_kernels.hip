@@ -43,10 +43,13 @@ namespace {
 // generic loop.
 //
 // A slice in device memory stores a row through a buffer descriptor of its own, whose range
-// check drops the lanes past the row's end without a branch; non-temporally: with three output
-// buffers in turn 42.0 us against 46.7 with plain stores (bf16 KV layer, 134 MB out, 16-row batches), with
-// one buffer that every call writes again, whose lines plain stores find in the last-level
-// cache, 41.6 against 40.3 (exec-masked plain stores before: 48.9 and 42.1; now 40.0 and 40.5).
+// check drops the lanes past the row's end without a branch, and non-temporally. bf16 rows in
+// slices of 8, us plain / non-temporal, with three payloads and outputs in turn: 134 MB out of
+// 256-B rows 47.1 / 42.3, of 400-B rows 59.4 / 48.6; 64 MB 24.7 / 19.7 and 32.5 / 22.4; 16 MB
+// 7.7 / 7.2 and 9.4 / 8.2; 2 MB alike. With one output that every call writes again, whose lines
+// plain stores find in the last-level cache: 134 MB 37.5 / 39.3 and 42.2 / 45.5; 64 MB 19.7 /
+// 19.7 and 21.5 / 22.2; 16 MB 7.4 / 7.2 and 8.7 / 7.1. A call does not know which of the two it
+// is, and fresh outputs gain more than the rewritten one loses.
 // A slice of rows of at most 128 words in pinned host memory (At::kMaskedStores) takes plain
 // stores under the row's lane mask: 24 MB out of 512-B rows 184 us with those and 189 through
 // descriptors, of 128-B rows 359 and 372.
@@ -1190,20 +1193,17 @@ hipError_t launch_decompress(const DevStream &s, const uint8_t *payload, uint64_
     // two dword loads per window from device memory, one 8-byte load from pinned host memory
     // (where a wave also takes whole rows: a tile's first and last lines would cross PCIe
     // for each of the tiles that share them)
-    auto launch = [&](auto kk, auto mr) {
-        if (s.payload_host) go(kk, mr, std::false_type{}, std::false_type{});
-        else if constexpr (decltype(kk)::value <= 2) go(kk, mr, std::true_type{}, std::false_type{});
+    const std::integral_constant<int, 4> four{};
+    auto narrow = [&](auto kk) {
+        if (s.payload_host) go(kk, four, std::false_type{}, std::false_type{});
+        else go(kk, four, std::true_type{}, std::false_type{});
     };
-    if (tiled) {
-        go(std::integral_constant<int, 2>{}, std::integral_constant<int, 4>{}, std::true_type{}, std::true_type{});
-        return hipGetLastError();
-    }
-    switch (k) {
-    case 1: launch(std::integral_constant<int, 1>{}, std::integral_constant<int, 4>{}); break;
-    case 2: launch(std::integral_constant<int, 2>{}, std::integral_constant<int, 4>{}); break;
-    case 4: launch(std::integral_constant<int, 4>{}, std::integral_constant<int, 2>{}); break;
-    default: launch(std::integral_constant<int, 8>{}, std::integral_constant<int, 1>{}); break;
-    }
+    if (tiled) go(std::integral_constant<int, 2>{}, four, std::true_type{}, std::true_type{});
+    else if (k == 1) narrow(std::integral_constant<int, 1>{});
+    else if (k == 2) narrow(std::integral_constant<int, 2>{});
+    else if (!s.payload_host) return hipErrorInvalidValue;   // (wide rows there have a tile table)
+    else if (k == 4) go(four, std::integral_constant<int, 2>{}, std::false_type{}, std::false_type{});
+    else go(std::integral_constant<int, 8>{}, std::integral_constant<int, 1>{}, std::false_type{}, std::false_type{});
     return hipGetLastError();
 }
 

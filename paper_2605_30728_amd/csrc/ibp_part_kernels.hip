@@ -19,7 +19,7 @@
 // Measured (us, strided words with a scan and a store per word -> this): a 134 MB bf16 KV
 // layer (524k rows of 64 words, 259 MB of HBM traffic) 50.2 -> 45.2, 82k sorted 400-B rows of
 // 1.2M 17.4 -> 13.8 (108 -> ~55 vector instructions per row; HBM bounds both now), 145k rows
-// of 60 words 14.5 -> 14.2, 82k rows under per-cluster Masks 30.0 -> 26.0.
+// of 60 words 14.5 -> 14.2, 82k rows under per-cluster Masks 30.0 -> 23.8.
 //
 // Under one Mask for the whole stream (ONE, the scheme as published) its words are set up
 // once per wave. Otherwise a batch of rows that share a cluster reuses its setup, and a
@@ -275,7 +275,9 @@ hipError_t launch_narrow_k(const DevStream &s, const uint8_t *payload, uint64_t 
         constexpr int P = decltype(pre)::value, S = decltype(src)::value;
         constexpr bool O = decltype(one_tag)::value;
         // windows as separate dword loads at K = 1 (524k rows: 45.2 us, 50.1 as one 8-byte
-        // load), as one 12-byte load at K = 2 (200k contiguous 512-B rows: 39 us, 48 split)
+        // load; from pinned host memory too: 9,879 rows of 16 words 15.1 and 16.2, 28,882 of 12
+        // words 27.7 and 28.7, rows of 40 words and more alike), as one 12-byte load at K = 2
+        // (200k contiguous 512-B rows: 39 us, 48 split)
         hipLaunchKernelGGL((k_part_narrow<K, MAXR, S, P, O, K == 1>), grid, block, 0, stream, s, payload, pay_base,
                            ids, sg, soff, first, n, o, seg, err);
     };

@@ -48,6 +48,7 @@ namespace ibp {
 namespace {
 
 constexpr uint64_t kSlack = 256;                 // readable bytes past any payload end
+static_assert(kSlack >= dev::kReadPast, "the kernels read past a payload's end");
 constexpr uint64_t kStageBytes = 128ull << 20;   // one staging buffer (a whole compressed 128 MiB
                                                   // KV layer in one copy: 0.98 of CR x raw H2D,
                                                   // against 0.85 in two 64 MiB copies)
@@ -57,19 +58,15 @@ constexpr int kIdSlots = 2;                       // host-id buffers in rotation
 // staged in, more are copied to the device first. Measured (us, copied -> in place): 208 ids
 // 14.4 -> 11.4, 4,160 22.2 -> 12.2, 16,640 24.6 -> 15.2, 53,248 34.5 -> 27.8, 163,840 77.6 ->
 // 76 (a copy costs a call and ~8 us of latency before the kernel; in place, a wave's 64 bytes
-// of ids cross PCIe as a 128-byte line, twice the bytes).
+// of ids cross PCIe as a 128-byte line, twice the bytes). Rows of several tiles, whose ids every
+// tile's wave reads, as well: 65,536 of 600 words 80.9 -> 68.8, of 4,096 words 311 -> 269 (8
+// pairs), 30,000 of 16,384 words 503 -> 442 (12 pairs).
 constexpr uint64_t kIdsInPlace = 65536;
 constexpr uint64_t kRowAlign = 128;               // PCIe line: row start of aligned zero-copy
 constexpr uint64_t kMaxRuns = 4096;               // copy pieces of a line-aligned cluster layout
 constexpr uint64_t kCountBytes = dev::kCountLines * dev::kCountStride * 8;   // cache counters
 constexpr uint64_t kBlk = 256;                    // rows per host packing task (a chunk
                                                   // holds tens of them, for 16 threads)
-
-// the host builds the compact metadata slots that the kernels read: one layout
-static_assert(meta_slot_bytes(8, 1) == dev::meta_slot_bytes(8, 1) && meta_slot_bytes(8, 2) == dev::meta_slot_bytes(8, 2) &&
-                  meta_slot_bytes(16, 4) == dev::meta_slot_bytes(16, 4) &&
-                  meta_slot_bytes(16, 8) == dev::meta_slot_bytes(16, 8),
-              "slot size");
 
 uint64_t round_up(uint64_t x, uint64_t a) { return (x + a - 1) / a * a; }
 
@@ -201,7 +198,7 @@ struct ibp_handle {
     ibp_desc d{};
     dev::DevStream ds{};
     uint32_t *d_meta = nullptr;
-    uint8_t *d_slots = nullptr;           // compact metadata of the row gathers (clustered, W <= 512)
+    uint8_t *d_slots = nullptr;           // compact metadata of the row gathers (clustered)
     dev::GroupInfo *d_groups = nullptr;   // DevStream::groups
     uint32_t *d_tile_bits = nullptr;      // DevStream::tile_bits
     uint8_t *d_row_lines = nullptr;       // line-packed row offsets (participation, rows <= 1092 B)

@@ -161,8 +161,8 @@ __device__ __forceinline__ void keep_order() { asm volatile("" ::: "memory"); }
 // A word's 64-bit window as two dword loads (dwords q and q + 1 of p). The compiler would
 // merge them into one 8-byte load, which is misaligned for every odd q; an opaque second
 // index keeps them two 4-byte loads. Measured: the 111M-row gather 830 -> 695 us, the bf16
-// KV layer decompress 46.3 -> 43.0 us; the thresholded kernels keep the merged load (their
-// KV layer measured 5% slower split, their gathers no faster).
+// KV layer decompress 46.3 -> 43.0 us. (k_part_batched and k_part_rows keep the merged load:
+// 5% slower split; k_part_narrow splits at one word per lane.)
 __device__ __forceinline__ void load_window(const uint32_t *__restrict__ p, uint32_t q, uint32_t &d0, uint32_t &d1) {
     uint32_t q1 = q + 1u;
     asm volatile("" : "+v"(q1));
