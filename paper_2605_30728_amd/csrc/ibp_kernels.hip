@@ -1183,12 +1183,20 @@ hipError_t launch_decompress(const DevStream &s, const uint8_t *payload, uint64_
     const auto *p = reinterpret_cast<const uint32_t *>(payload);
     auto *o = static_cast<uint32_t *>(out);
     dim3 grid((unsigned)blocks), block(kBlock);
+    // Rows of at most 64 words in pinned host memory: three or four blocks per CU, by LDS that no
+    // kernel uses (160 KB per CU). Eight keep more reads in flight than the link serves, over a
+    // stretch of memory that grows with them, and rows that start on lines of their own suffer
+    // most. us, eight / four / three, and with the 64-bit divisions that used to delay every wave's
+    // first read: 24 MB out of 156-B aligned rows of 16-row clusters 431.9 / 403.8 / 386.9 / 397.6,
+    // of 40-B ones 1643 / 1500 / 1455 / 1528; back to back, 156 B 266.1 / 256.1 / 245.2 / 257.2,
+    // 40 B 308.5 / 301.9 / 316.0 / 311.2. Rows of 65 words and more: alike, or up to 3% slower.
+    const uint32_t lds = !s.payload_host || k > 1 ? 0 : (s.W <= 12 ? 40u << 10 : 53u << 10);
     const RangeCall call{s.meta,    s.index, s.groups, s.tile_bits, pay_base,    first,           first + n,
                          units,     s.W,     s.G,      s.row_align, s.tiles128, (uint32_t)blocks};
     auto go = [&](auto kk, auto mr, auto split, auto tile) {
         constexpr int KK = decltype(kk)::value, MR = decltype(mr)::value;
         constexpr bool SP = decltype(split)::value, TI = decltype(tile)::value;
-        hipLaunchKernelGGL((k_decompress<KK, MR, SP, TI>), grid, block, 0, stream, call, p, o);
+        hipLaunchKernelGGL((k_decompress<KK, MR, SP, TI>), grid, block, lds, stream, call, p, o);
     };
     // two dword loads per window from device memory, one 8-byte load from pinned host memory
     // (where a wave also takes whole rows: a tile's first and last lines would cross PCIe
