@@ -198,9 +198,9 @@ struct ibp_handle {
     ibp_desc d{};
     dev::DevStream ds{};
     uint32_t *d_meta = nullptr;
-    uint8_t *d_slots = nullptr;           // compact metadata of the row gathers (clustered)
-    dev::GroupInfo *d_groups = nullptr;   // DevStream::groups
-    uint32_t *d_tile_bits = nullptr;      // DevStream::tile_bits
+    uint8_t *d_gather = nullptr;          // clustered: DevStream's slots, groups and tile_bits
+    dev::GroupInfo *d_groups = nullptr;   // (in d_gather)
+    uint32_t *d_tile_bits = nullptr;      // (in d_gather)
     uint8_t *d_row_lines = nullptr;       // line-packed row offsets (participation, rows <= 1092 B)
     uint64_t *d_index = nullptr;
     uint8_t *d_payload = nullptr;
@@ -307,15 +307,13 @@ ibp_status check_handle(ibp_handle *h, const CallScope &cs) {
 // Frees everything a handle owns except the struct itself.
 void release_handle(ibp_handle *h) {
     dev_free(h->d_meta);
-    dev_free(h->d_slots);
-    dev_free(h->d_groups);
-    dev_free(h->d_tile_bits);
+    dev_free(h->d_gather);
     dev_free(h->d_row_lines);
     dev_free(h->d_index);
     dev_free(h->d_payload);
     dev_free(h->d_err);
     h->d_meta = nullptr;
-    h->d_slots = nullptr;
+    h->d_gather = nullptr;
     h->d_groups = nullptr;
     h->d_tile_bits = nullptr;
     h->d_row_lines = nullptr;
@@ -766,29 +764,34 @@ ibp_status open_impl(const void *stream, uint64_t stream_bytes, int device, uint
     // a wave reads with one load, and else lane-order ones, where a load covers a stretch of
     // the row's lines of its own
     const bool word_order = flags == IBP_OPEN_PAYLOAD_DEVICE || flags == IBP_OPEN_PAYLOAD_HOST || W <= 128;
+    std::vector<uint8_t> slots;
+    uint32_t P = 0;
     if (d.flags == 0 && (W <= 512 || word_order)) {
         // the row gathers read a cluster's metadata for every row they decode: when every
         // cluster fits one, give each a compact slot as well
         const uint32_t K = (uint32_t)dev::words_per_lane(W);
         check_alloc();
-        std::vector<uint8_t> slots;
-        const uint32_t P = build_meta_slots(v.meta(), d.n_groups, W, K, *h->pool, slots, word_order);
-        if (P) {
-            if (dev_alloc(&h->d_slots, slots.size()) != hipSuccess)
-                return bail(fail(IBP_ENOMEM, "device allocation for metadata failed"));
-            if (hipMemcpy(h->d_slots, slots.data(), slots.size(), hipMemcpyHostToDevice) != hipSuccess)
-                return bail(fail(IBP_EHIP, "metadata upload failed"));
-            h->ds.slot_pairs = P;
-            h->ds.slot_bytes = (uint32_t)(word_order ? meta_slot_bytes_of(P, W) : meta_slot_bytes(P, K));
-            h->ds.word_order = word_order;
-        }
+        P = build_meta_slots(v.meta(), d.n_groups, W, K, *h->pool, slots, word_order);
+        h->ds.slot_pairs = P;
+        h->ds.slot_bytes = (uint32_t)(word_order ? meta_slot_bytes_of(P, W) : meta_slot_bytes(P, K));
+        h->ds.word_order = P && word_order;
     }
-    if (d.flags == 0 && word_order && (h->d_slots || W > 128)) {
-        h->ds.tiles128 = (W + 127) / 128;
+    const bool places = d.flags == 0 && word_order && (P || W > 128);   // where clusters and tiles start
+    if (P || places) {
+        // one allocation (whole 128-byte lines of slots, groups, tile bits): each is ~10 us of
+        // a small stream's opening
+        h->ds.tiles128 = places ? (W + 127) / 128 : 0;
         const uint64_t ng = std::max<uint64_t>(d.n_groups, 1);
-        if (dev_alloc(&h->d_groups, ng * sizeof(dev::GroupInfo)) != hipSuccess ||
-            (W > 128 && dev_alloc(&h->d_tile_bits, ng * 4 * h->ds.tiles128) != hipSuccess))
+        const uint64_t groups_at = slots.size(), tiles_at = groups_at + (places ? ng * sizeof(dev::GroupInfo) : 0);
+        if (dev_alloc(&h->d_gather, tiles_at + (W > 128 ? ng * 4 * h->ds.tiles128 : 0)) != hipSuccess)
             return bail(fail(IBP_ENOMEM, "device allocation for metadata failed"));
+        if (P) {
+            if (hipMemcpy(h->d_gather, slots.data(), slots.size(), hipMemcpyHostToDevice) != hipSuccess)
+                return bail(fail(IBP_EHIP, "metadata upload failed"));
+            h->ds.slots = h->d_gather;
+        }
+        if (places) h->d_groups = reinterpret_cast<dev::GroupInfo *>(h->d_gather + groups_at);
+        if (places && W > 128) h->d_tile_bits = reinterpret_cast<uint32_t *>(h->d_gather + tiles_at);
     }
     if ((d.flags & IBP_STREAM_PARTICIPATION) && d.n_rows > 0 && d.n_rows <= ~0ull / dev::kRowLineRows &&
         (uint64_t)d.row_bytes * dev::kRowLineRows <= 0xFFFF) {
@@ -839,7 +842,6 @@ ibp_status open_impl(const void *stream, uint64_t stream_bytes, int device, uint
         if (hipEventCreateWithFlags(&h->ev_ids_free[j], hipEventDisableTiming) != hipSuccess)
             return bail(fail(IBP_EHIP, "event creation failed"));
     h->ds.meta = h->d_meta;
-    h->ds.slots = h->d_slots;
     h->ds.groups = h->d_groups;
     h->ds.tile_bits = h->d_tile_bits;
     h->ds.row_lines = h->d_row_lines;
@@ -1080,7 +1082,7 @@ ibp_status ibp_get_stats(ibp_handle *h, ibp_stats *st) {
     if (!h) return fail(IBP_EINVAL, "handle is null");
     if (!cs.ok()) return fail(IBP_ESTATE, cs.closed() ? "handle is closed" : "handle is in use by another thread");
     *st = h->stats;
-    st->gather_meta_bytes = h->d_slots ? h->ds.slot_bytes : 2ull * h->d.row_bytes;
+    st->gather_meta_bytes = h->ds.slots ? h->ds.slot_bytes : 2ull * h->d.row_bytes;
     return IBP_OK;
 }
 

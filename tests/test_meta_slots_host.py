@@ -1,5 +1,6 @@
 """The metadata slots' host builder on the CPU: it allocates nothing on the pool's threads (an
-exception there would end the process, not the call), whatever the rows' width."""
+exception there would end the process, not the call), whatever the rows' width, and tells pairs
+of one 32-bit tag apart."""
 import os
 import subprocess
 
@@ -27,10 +28,11 @@ int main(int argc, char **argv) {
     caller = true;
     const uint32_t W = (uint32_t)std::atoi(argv[1]);
     const bool word_order = argv[2][0] == '1';
+    const bool tagged = argv[3][0] == '1';   // every pair's tag is 0
     const uint64_t groups = 64;
     std::vector<uint32_t> meta(groups * 2 * W);
     for (uint64_t g = 0; g < groups; ++g)
-        for (uint32_t w = 0; w < W; ++w) meta[(2 * g) * W + w] = w % 11, meta[(2 * g + 1) * W + w] = 0;
+        for (uint32_t w = 0; w < W; ++w) meta[(2 * g) * W + w] = w % 11, meta[(2 * g + 1) * W + w] = tagged ? (w % 11) * 0x9E3779B1u : 0;
     ibp::Pool pool(4);
     std::vector<uint8_t> slots;
     failing = true;
@@ -42,6 +44,7 @@ int main(int argc, char **argv) {
     for (uint64_t g = 0; g < groups; ++g)
         for (uint32_t w = 0; w < W; ++w) {
             const uint64_t at = word_order ? w : (uint64_t)(W <= 64 ? 1 : 8) * (w % 64) + w / 64;
+            if (slots[g * S + 8 * (w % 11)] != w % 11) return 3;
             if (((slots[g * S + 8 * P + at / 2] >> (4 * (at % 2))) & 15) != w % 11) return 2;
         }
     return 0;
@@ -59,6 +62,7 @@ def program(tmp_path_factory):
     return str(d / "slots")
 
 
+@pytest.mark.parametrize("tagged", [0, 1])
 @pytest.mark.parametrize("W,word_order", [(11, 0), (64, 1), (500, 0), (512, 1), (513, 1), (20_000, 1)])
-def test_no_memory_on_the_pool_threads(program, W, word_order):
-    assert subprocess.run([program, str(W), str(word_order)]).returncode == 0
+def test_no_memory_on_the_pool_threads(program, W, word_order, tagged):
+    assert subprocess.run([program, str(W), str(word_order), str(tagged)]).returncode == 0
