@@ -10,8 +10,8 @@
 // 33.7 us they took. So everything that depends only on a cluster is computed for several
 // rows at once, and everything that depends only on a lane is a constant:
 //
-//   * A wave takes 64/P work items per pass (P = 8 or 16 pairs per slot; an item is a row,
-//     or a tile of 64K words of a wider row). Lane l holds pair l mod P of item l / P: one
+//   * A wave takes 64/P work items per pass (P = 8 or 16 lanes, at least the pairs of a slot;
+//     an item is a row, or a tile of 64K words of a wider row). Lane l holds pair l mod P of item l / P: one
 //     load fetches every item's pairs, one pass over the lanes turns each pair into its
 //     deposit (where up to four runs of variant bits go and how far they shift), and one
 //     16-byte LDS write per lane publishes them.
@@ -31,7 +31,7 @@
 // copy's rate), 1.5M shuffled 512-B rows of 3M 293 -> 235, 16k random 4-KB rows 230 -> 19.4
 // (there each row's 8 KB of Mask/Bitval words are replaced by its cluster's 640-byte slot).
 // From pinned host memory, us: 82k sorted 400-B rows 486 -> 468 (their distinct 128-B lines at
-// the link's 57 GB/s take 469), 53k Zipf lookups behind a cache that misses 16% 62.3 -> 60.9
+// the link's 57 GB/s take 469), 53k Zipf lookups behind a cache that misses 16% 62.2 -> 61.2
 // (lines of the misses: 50). Measured and not kept: half the items in flight (+1-8%), plain stores (+6-24%), one
 // 12-byte load per window for K <= 2 (+4-5%) and three 4-byte ones for K = 4 (+17%).
 #include <algorithm>
@@ -90,12 +90,14 @@ __device__ __forceinline__ uint32_t deposit(const PairDeposit &e, uint32_t x) {
 
 enum { kFromIds = 0, kFromStage = 1, kFromCache = 2 };   // where an item's row is found
 
-// SPLIT: a window as separate dword loads.
+// SPLIT: a window as separate dword loads. `blocks`, `block_waves`: the launch's blocks and waves
+// per block, as arguments: read from the launch they would bring 256 bytes of implicit ones.
 template <int K, int P, int SRC, bool TILED, bool SPLIT>
 __device__ __forceinline__ void gather_slots(const DevStream &s, const CacheView &c, const uint8_t *__restrict__ pay,
                                              const int64_t *__restrict__ ids, const uint32_t *__restrict__ sg,
                                              const uint32_t *__restrict__ soff, uint64_t n_items, uint32_t tiles,
-                                             uint64_t tiles_magic, uint32_t *__restrict__ out,
+                                             uint32_t blocks, uint32_t block_waves, uint64_t tiles_magic,
+                                             uint32_t *__restrict__ out,
                                              unsigned long long *err) {
     constexpr int IT = kWave / P;                       // items of the wave
     constexpr int GROUP = K <= 2 || IT < 4 ? IT : 4;    // items whose windows are in flight together
@@ -105,11 +107,12 @@ __device__ __forceinline__ void gather_slots(const DevStream &s, const CacheView
     const uint32_t l = lane_id();
     const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
     PairDeposit *__restrict__ tab = s_tab + wave * kWave;
-    const uint64_t base = ((uint64_t)xcd_block(blockIdx.x, gridDim.x) * kWavesPerBlock + wave) * IT;
+    const uint64_t base = ((uint64_t)xcd_block(blockIdx.x, blocks) * block_waves + wave) * IT;
     if (base >= n_items) return;
     const uint32_t W = s.W;
     const uint32_t cnt = (uint32_t)min((uint64_t)IT, n_items - base);
     const uint32_t own = l / P;
+    const uint32_t pair_at = P == 8 ? l % 8 : l & (s.slot_pairs - 1);   // (P 16 also takes slots of 8 pairs)
     const uint64_t item = base + min(own, cnt - 1);   // lanes past the end repeat the last item
     uint64_t r = item;
     uint32_t t = 0;
@@ -129,7 +132,7 @@ __device__ __forceinline__ void gather_slots(const DevStream &s, const CacheView
         byte = soff[r];
         len = soff[r + 1] - (uint32_t)byte;
         slot_l = s.slots + g * s.slot_bytes;
-        pair = reinterpret_cast<const uint2 *>(slot_l)[l % P];
+        pair = reinterpret_cast<const uint2 *>(slot_l)[pair_at];
     } else {
         const int64_t id = ids[r];
         valid = id >= 0 && (uint64_t)id < s.n_rows;
@@ -137,13 +140,13 @@ __device__ __forceinline__ void gather_slots(const DevStream &s, const CacheView
         if constexpr (SRC == kFromCache) probe = cache_probe_begin(c, uid);
         g = s.G == 1 ? uid : __umul64hi(uid, s.g_magic);
         slot_l = s.slots + g * s.slot_bytes;
-        pair = reinterpret_cast<const uint2 *>(slot_l)[l % P];
+        pair = reinterpret_cast<const uint2 *>(slot_l)[pair_at];
         const GroupInfo gi = s.groups[g];
         byte = valid ? gi.off + (uint64_t)(uint32_t)(uid - g * s.G) * gi.stride : 0;
         len = valid ? gi.stride : 0u;   // (an invalid id reads nothing)
     }
     // every item's pair indices of the lane's words, 4 bits each
-    const uint8_t *const idx_l = slot_l + 8 * P + (TILED ? t * (32u * K) : 0u);
+    const uint8_t *const idx_l = slot_l + (P == 8 ? 64u : 8u * s.slot_pairs) + (TILED ? t * (32u * K) : 0u);
     uint32_t idx[IT];
 #pragma unroll
     for (int i = 0; i < IT; ++i) {
@@ -320,18 +323,22 @@ __global__ __launch_bounds__(kBlock, K <= 2 ? 8 : 5) void k_gather_slots(DevStre
                                                                          const uint32_t *__restrict__ sg,
                                                                          const uint32_t *__restrict__ soff,
                                                                          uint64_t n_items, uint32_t tiles,
+                                                                         uint32_t blocks, uint32_t block_waves,
                                                                          uint64_t tiles_magic,
                                                                          uint32_t *__restrict__ out,
                                                                          unsigned long long *err) {
-    gather_slots<K, P, SRC, TILED, SPLIT>(s, CacheView{}, pay, ids, sg, soff, n_items, tiles, tiles_magic, out, err);
+    gather_slots<K, P, SRC, TILED, SPLIT>(s, CacheView{}, pay, ids, sg, soff, n_items, tiles, blocks, block_waves,
+                                          tiles_magic, out, err);
 }
 
 template <int K, int P>
 __global__ __launch_bounds__(kBlock, 8) void k_cache_gather_slots(DevStream s, CacheView c,
                                                                   const int64_t *__restrict__ ids, uint64_t n_items,
+                                                                  uint32_t blocks, uint32_t block_waves,
                                                                   uint32_t *__restrict__ out,
                                                                   unsigned long long *err) {
-    gather_slots<K, P, kFromCache, false, false>(s, c, c.host_payload, ids, nullptr, nullptr, n_items, 1, 0, out, err);
+    gather_slots<K, P, kFromCache, false, false>(s, c, c.host_payload, ids, nullptr, nullptr, n_items, 1, blocks,
+                                                 block_waves, 0, out, err);
 }
 
 // Per cluster: where its rows start, their distance, and the bit at which every 128-word
@@ -368,28 +375,42 @@ hipError_t launch_gather_slots(const DevStream &s, const CacheView *cache, const
     auto *o = static_cast<uint32_t *>(out);
     const uint32_t tiles = s.W <= 256 ? 1u : (s.W + 255u) / 256u;
     const uint64_t items = n * tiles;
-    const uint32_t per = (uint32_t)kWave / s.slot_pairs;
+    // Few items: 16 lanes each also where slots hold 8 pairs (four items per wave instead of eight,
+    // which follow one another at several points), and a wave per block, so that they spread over
+    // the CUs. us on the GPU, 8 lanes and 4 waves per block / 16 and 4 / 16 and 1, clusters of at
+    // most 8 pairs in device memory:
+    //   rows of 100 words  100: 4.08 / 3.20 / 3.09   4,000: 4.33 / 3.46 / 3.43   8,000: 4.54 / 3.85 / 3.94
+    //                      16,000: 4.91 / 4.55 / 4.85
+    //   rows of 300 words  100: 5.42 / 3.93 / 3.82   4,000 (8,000 items): 5.84 / 4.86 / 4.87
+    //   rows of 1,000 words  4,000 (16,000 items): 7.27 / 6.81 / 7.10   8,000: 10.88 / 11.03 / 11.05
+    // in host memory, 100 words, 400 rows 7.54 / 6.77 / 6.63; 520 of 100 words behind a cache that
+    // misses most 8.62 / 8.10 / 5.84.
+    const bool pairs16 = s.slot_pairs == 16 || items <= 16384;
+    const uint32_t per = pairs16 ? 4 : 8;
     const uint64_t waves = (items + per - 1) / per;
-    const uint64_t blocks = blocks_of_waves(waves);
+    const uint32_t block_waves = waves <= 1024 ? 1 : kWavesPerBlock;
+    const uint64_t blocks = (waves + block_waves - 1) / block_waves;
     if (too_many_blocks(blocks, n))
         return in_halves(n, [&](uint64_t i, uint64_t count) {
             return launch_gather_slots(s, cache, payload, from(ids, i), from(sg, i), from(soff, i), count, o + i * s.W,
                                        err, stream);
         });
-    const dim3 grid((unsigned)blocks), block(kBlock);
+    const dim3 grid((unsigned)blocks), block(kWave * block_waves);
     auto go = [&](auto k, auto tiled, auto src, auto split) {
         constexpr int K = decltype(k)::value, SRC = decltype(src)::value;
         constexpr bool T = decltype(tiled)::value, SP = decltype(split)::value;
         auto pairs = [&](auto p) {
             constexpr int P = decltype(p)::value;
             if constexpr (SRC == kFromCache)
-                hipLaunchKernelGGL((k_cache_gather_slots<K, P>), grid, block, 0, stream, s, *cache, ids, items, o, err);
+                hipLaunchKernelGGL((k_cache_gather_slots<K, P>), grid, block, 0, stream, s, *cache, ids, items,
+                                   (uint32_t)blocks, block_waves, o, err);
             else
                 hipLaunchKernelGGL((k_gather_slots<K, P, SRC, T, SP>), grid, block, 0, stream, s, payload, ids, sg,
-                                   soff, items, tiles, div_magic(tiles), o, err);
+                                   soff, items, tiles, (uint32_t)blocks, block_waves, div_magic(tiles),
+                                   o, err);
         };
-        if (s.slot_pairs == 8) pairs(std::integral_constant<int, 8>{});
-        else pairs(std::integral_constant<int, 16>{});
+        if (pairs16) pairs(std::integral_constant<int, 16>{});
+        else pairs(std::integral_constant<int, 8>{});
     };
     // A window of device memory is read as separate dwords at one or two words per lane (4-5%
     // faster than one load) and as one load at four (17% faster). From host memory always as

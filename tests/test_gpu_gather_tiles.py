@@ -233,3 +233,41 @@ def test_more_clusters_than_one_launch(torch):
         ibp.ibp_gather_decompress_device(h, torch.from_numpy(ids).cuda(), out)
         torch.cuda.synchronize()
         assert np.array_equal(out.cpu().numpy().view(np.uint32), rows[ids])
+
+
+@pytest.mark.parametrize("kind", sorted(KINDS))
+@pytest.mark.parametrize("W,where", [(1, "device"), (64, "device"), (65, "device"), (128, "device"), (129, "device"),
+                                     (256, "device"), (257, "device"), (1025, "device"), (64, "zero_copy"),
+                                     (65, "zero_copy"), (128, "zero_copy"), (33, "cache"), (100, "cache")])
+def test_small_and_large_calls(torch, W, kind, where):
+    """The two lane counts per item under slots of 8 pairs and the two sizes of a block, to either
+    side of both lines (4,096 and 16,384 items), with ids outside the table among the last."""
+    G, L = 40, 4 * W
+    n = G * len(KINDS[kind]) * 3 + 3
+    rows = rows_of_runs(W, n, G, KINDS[kind], seed=W + 7)
+    rng = np.random.default_rng(W)
+    tiles = (W + 255) // 256
+    flags = ibp.IBP_OPEN_PAYLOAD_DEVICE if where == "device" else ibp.IBP_OPEN_PAYLOAD_HOST_ZERO_COPY
+    print(f"[gather tiles] small and large W={W} {kind} {where}", file=sys.stderr, flush=True)
+    with ibp.ibp_open(oracle.compress(rows, G), 0, flags) as h:
+        cache = ibp.ibp_cache_create(h, rng.permutation(n)[:n // 2].astype(np.int64)) if where == "cache" else None
+        call = (lambda i, o, c: ibp.ibp_cache_gather(cache, i, o, out_cap=c)) if cache else \
+            (lambda i, o, c: ibp.ibp_gather_decompress_device(h, i, o, out_cap=c))
+        total = 0
+        for items in (4096, 4100, 16384, 16393):
+            count = -(-items // tiles)
+            ids = rng.integers(0, n, size=count).astype(np.int64)
+            sent = ids.copy()
+            sent[-7:-3] = (-1, n, 1 << 40, -(1 << 40))
+            out = torch.full((count * L + 64,), 0xA5, dtype=torch.uint8, device="cuda")
+            call(torch.from_numpy(sent).cuda(), out, count * L)
+            torch.cuda.synchronize()
+            want = rows[ids].copy()
+            want[-7:-3] = 0
+            got = out[:count * L].cpu().numpy().reshape(count, L)
+            assert np.array_equal(got, want), (count, np.flatnonzero((got != want).any(1))[:8])
+            assert (out[count * L:].cpu().numpy() == 0xA5).all(), "wrote past the output"
+            total += 4
+        assert cache or ibp.ibp_device_errors(h) == total
+        if cache:
+            ibp.ibp_cache_destroy(cache)
