@@ -49,14 +49,15 @@ struct PartRow {
 
 // PRE: participation dwords per row (1, 2 or 4). SPLIT: a window as separate dword loads.
 template <int K, int MAXR, int SRC, int PRE, bool ONE, bool SPLIT>
-__global__ __launch_bounds__(kBlock, K == 1 ? 8 : (!ONE ? 5 : (PRE == 1 ? 7 : 8))) void k_part_narrow(DevStream s, const uint8_t *__restrict__ pay,
+__global__ __launch_bounds__(kBlock, K == 1 ? 8 : (!ONE ? 5 : (PRE == 2 ? 8 : 7))) void k_part_narrow(DevStream s, const uint8_t *__restrict__ pay,
                                                            uint64_t pay_base, const int64_t *__restrict__ ids,
                                                            const uint32_t *__restrict__ sg,
                                                            const uint32_t *__restrict__ soff, uint64_t first,
                                                            uint64_t n, uint32_t *__restrict__ out, uint32_t seg,
-                                                           unsigned long long *err) {
+                                                           uint32_t block_waves, unsigned long long *err) {
     constexpr int RB = K == 1 ? 8 : 4;
-    const uint64_t i0 = wave_slot() * seg;
+    const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
+    const uint64_t i0 = ((uint64_t)blockIdx.x * block_waves + wave) * seg;
     if (i0 >= n) return;
     const uint32_t cnt = (uint32_t)min((uint64_t)seg, n - i0);
     const uint32_t l = lane_id();
@@ -138,7 +139,14 @@ __global__ __launch_bounds__(kBlock, K == 1 ? 8 : (!ONE ? 5 : (PRE == 1 ? 7 : 8)
         store_words<K>(row_rsrc(out_seg + i * W, on ? 4u * W : 0u), l * (4u * K), v);
     };
     // the word's packed bits x, rebuilt by `word` when its chunk is compressed
-    auto rebuild = [&](const PartRow<K> &row, auto word, uint32_t (&v)[K]) {
+    auto rebuild = [&](PartRow<K> &row, auto word, uint32_t (&v)[K]) {
+        if constexpr (PRE == 4) {
+            // the window is needed from here on: shifted earlier, to save registers, every row's
+            // load was waited for before the next one was issued (100 rows of 104 words in host
+            // memory, four-byte chunks, 9.4 us on the GPU; in flight together 6.2)
+#pragma unroll
+            for (int k = 0; k <= K; ++k) asm volatile("" : "+v"(row.d[k]));
+        }
         const uint32_t lo = __builtin_amdgcn_alignbit(row.d[1], row.d[0], row.first);
         v[0] = bit_select(row.sel[0], word(0, lo), lo);
         if constexpr (K == 2) {
@@ -261,15 +269,20 @@ hipError_t launch_narrow_k(const DevStream &s, const uint8_t *payload, uint64_t 
     constexpr int RB = K == 1 ? 8 : 4;
     const bool one = (uint64_t)s.G >= s.n_rows;   // a single cluster
     const uint32_t nb = n / ((K == 1 ? 16384ull : 8192ull) * RB) >= 1 && (K == 2 || one) ? 2 : 1;
-    const uint32_t seg = RB * nb;
+    // Requests under per-cluster Masks from pinned host memory, one word per lane: half a batch per
+    // wave, since a wave decodes its halves one after the other, a round trip over PCIe each.
+    const uint32_t seg = K == 1 && !one && ids && s.payload_host ? RB / 2 : RB * nb;
     const uint64_t waves = (n + seg - 1) / seg;
-    const uint64_t blocks = blocks_of_waves(waves);
+    // few waves spread over the CUs, except where neighbours share lines that cross PCIe (1,000
+    // contiguous rows of 72 words in host memory 14.2 us in blocks of four waves, 15.8 of one)
+    const uint32_t block_waves = waves <= 1024 && (!s.payload_host || ids) ? 1 : kWavesPerBlock;
+    const uint64_t blocks = (waves + block_waves - 1) / block_waves;
     if (too_many_blocks(blocks, n))
         return in_halves(n, [&](uint64_t i, uint64_t count) {
             return launch_narrow_k<K, MAXR>(s, payload, pay_base, from(ids, i), from(sg, i), from(soff, i), first + i,
                                             count, o + i * s.W, err, stream);
         });
-    const dim3 grid((unsigned)blocks), block(kBlock);
+    const dim3 grid((unsigned)blocks), block(kWave * block_waves);
     const uint32_t chunks = s.W / s.part_m;
     auto go = [&](auto pre, auto one_tag, auto src) {
         constexpr int P = decltype(pre)::value, S = decltype(src)::value;
@@ -279,7 +292,7 @@ hipError_t launch_narrow_k(const DevStream &s, const uint8_t *payload, uint64_t 
         // words 27.7 and 28.7, rows of 40 words and more alike), as one 12-byte load at K = 2
         // (200k contiguous 512-B rows: 39 us, 48 split)
         hipLaunchKernelGGL((k_part_narrow<K, MAXR, S, P, O, K == 1>), grid, block, 0, stream, s, payload, pay_base,
-                           ids, sg, soff, first, n, o, seg, err);
+                           ids, sg, soff, first, n, o, seg, block_waves, err);
     };
     auto go_src = [&](auto pre, auto one_tag) {
         if (ids) go(pre, one_tag, std::integral_constant<int, kSrcIds>{});

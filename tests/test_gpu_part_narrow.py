@@ -81,3 +81,22 @@ def test_two_batches_per_wave(torch, W, G):
             assert np.array_equal(got, rows[n - count:]), count
             got = take(torch, lambda o: ibp.ibp_gather_decompress(h, ids[:count], o, out_cap=count * L), count, L)
             assert np.array_equal(got, rows[ids[:count]]), count
+
+
+@pytest.mark.parametrize("G", [40, 1 << 20])
+@pytest.mark.parametrize("placement", sorted(FLAGS))
+@pytest.mark.parametrize("W,m", [(20, 1), (64, 2), (100, 1), (100, 2)])
+def test_blocks_of_one_wave(torch, W, m, placement, G):
+    """The most rows whose waves are a block each (1,024 waves) and the fewest whose are not; from
+    host memory under per-cluster Masks half as many rows per wave at one word per lane."""
+    L = 4 * W
+    rows = structured_rows("floats", 8201, L, seed=W)
+    stream = ibp.ibp_compress_ex(rows, G, 4 * m, (4, 5))
+    rng = np.random.default_rng(W)
+    with ibp.ibp_open(stream, 0, FLAGS[placement]) as h:
+        for count in (4096, 4097, 8192, 8201):
+            got = take(torch, lambda o: ibp.ibp_decompress(h, 8201 - count, count, o, out_cap=count * L), count, L)
+            assert np.array_equal(got, rows[8201 - count:]), count
+            ids = rng.integers(0, 8201, size=count).astype(np.int64)
+            got = take(torch, lambda o: ibp.ibp_gather_decompress(h, ids, o, out_cap=count * L), count, L)
+            assert np.array_equal(got, rows[ids]), count
