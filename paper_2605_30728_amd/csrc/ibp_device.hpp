@@ -38,9 +38,9 @@ struct DevStream {
     uint32_t slot_bytes;
     uint32_t word_order;     // 1: the slots' indices are in word order, and the gathers are
                              // launch_gather_slots's
-    // clustered scheme, payload or stage in device memory, and slots or rows of more than
-    // 128 words: where each cluster's rows are, and for those wider rows the packed bit at
-    // which every 128-word tile of a row starts, tiles128 = ceil(W / 128) entries per cluster
+    // clustered scheme, with word-order slots, or payload or stage in device memory and rows of
+    // more than 128 words: where each cluster's rows are, and for those wider rows the packed
+    // bit at which every 128-word tile of a row starts, tiles128 = ceil(W / 128) per cluster
     const GroupInfo *groups;
     const uint32_t *tile_bits;
     uint32_t tiles128;
